@@ -86,6 +86,8 @@ struct HeviParams {
     const double *lev;   // [n_z][kLevW]
     const double *gz;    // [n_z][2N+1] DSS'd vertical derivative stencil
     double gamma, g;
+    const double *cst;   // [kCst]: D, then the EOS series
+    const double *hz2;   // [nel_z] 2 / h_z of each element layer
 };
 
 // L_v x on levels k0 .. k1-1 of lattice column col (the vertical operator
@@ -170,6 +172,10 @@ hipError_t launch_lv_resid(const HeviParams &h, double alpha, const double *b, c
 hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb &lc, double *out,
                              hipStream_t s);
 hipError_t launch_gmres(const HeviParams &h, const GmresArgs &g, hipStream_t s);
+// The forms with z-elements on lanes: columns of up to 16 elements, restart
+// lengths up to kGmresColM
+bool gmres_lanes_ok(const HeviParams &h, const GmresArgs &g);
+hipError_t launch_gmres_lanes(const HeviParams &h, const GmresArgs &g, hipStream_t s);
 
 // ---- tensor hyper-diffusion (box elements: one assembled 1D operator per direction)
 struct HyperParams {
@@ -253,6 +259,7 @@ hipError_t launch_ri(const RiParams &p, const double *q, bool center_given, doub
                      int *count, double *result, const double *z, const RiWork &w, hipStream_t s);
 
 constexpr int kGmresRegM = 10;        // restart length of the register-basis GMRES
+constexpr int kGmresColM = 20;        // longest restart of the two-lanes-per-element GMRES
 constexpr int kGmresRegSlots = 4;     // unknowns per lane it supports (3 n_z <= 256)
 constexpr int kGmresSchurSlots = 2;   // Schur form: interior w levels up to 128
 

@@ -861,6 +861,7 @@ HeviParams hevi_params(const nh_ctx *c)
     h.nx = c->n[0]; h.ny = c->n[1]; h.nz = c->n[2]; h.N = c->N;
     h.lev = c->lev; h.gz = c->gz;
     h.gamma = c->phys.cp / c->phys.cv; h.g = c->phys.g;
+    h.cst = c->cst; h.hz2 = c->hz2;
     return h;
 }
 
