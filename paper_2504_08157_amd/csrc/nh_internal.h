@@ -41,6 +41,7 @@ struct StageParams {
     int ntx, nty;
     double fcor, g, gamma;
     int stream;            // stream q^n, the heating and the result past the caches
+    int shape, nchunk;     // variant 0: tile shape and runs per column (stage_plan); 0, 1: whole columns
 };
 
 // States of at least this many bytes per array are streamed past the
@@ -338,6 +339,9 @@ hipError_t launch_mass(const GeomParams &g, double *M, hipStream_t s);
 hipError_t launch_diag(const GeomParams &g, const double *q, double *partials, double *out8,
                        hipStream_t s);
 void stage_tile(int N, int variant, int *tx, int *ty);
+// Tile shape (0 .. 3) and runs per column of the single-context stage launch
+// with tile variant 0.
+void stage_plan(int N, int nx, int ny, int nelz, int *shape, int *nchunk);
 constexpr int kTileVariants = 3;
 
 }  // namespace nh

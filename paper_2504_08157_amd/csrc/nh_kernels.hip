@@ -104,9 +104,16 @@ struct StageShape {
 // LDS column, sources, and the RK combination.  The element below's
 // contribution at the shared bottom level is carried in registers by the
 // threads that own the bottom level (same threads for every element).
-template <int N, int AX, int AY, typename T>
-__device__ __forceinline__ void stage_body(const StageParams &p, const int tile, const int tid)
+//
+// SPLIT: the workgroup walks only the elements ez0 .. ez1-1 (the lower
+// neighbour's contribution to its bottom level is recomputed from that
+// element's levels of the tile's own columns); otherwise the whole column.
+// Every node is computed with the same arithmetic in the same order.
+template <int N, int AX, int AY, typename T, bool SPLIT = false>
+__device__ __forceinline__ void stage_body(const StageParams &p, const int tile, const int tid, const int ez0_ = 0,
+                                           const int ez1_ = 0)
 {
+    const int ez0 = SPLIT ? ez0_ : 0, ez1 = SPLIT ? ez1_ : p.nelz;
     using S = StageShape<N, AX, AY>;
     constexpr int N1 = S::N1, TX = S::TX, TY = S::TY, NCOL = S::NCOL, NOWN = S::NOWN;
     constexpr int NT = S::NT, PX = S::PX, PS = S::PS, NSP = S::NSP, NC = S::NC;
@@ -209,9 +216,10 @@ __device__ __forceinline__ void stage_body(const StageParams &p, const int tile,
         smap[sn] = ok ? ((uint32_t)xg + nx * (uint32_t)yg) * 8u : 0xffffffffu;
         sidx[sn] = (uint16_t)(py * PX + px);
     }
+    const int kst = (SPLIT && ez0 > 0 ? ez0 - 1 : 0) * N;   // first staged level
     for (int i = tid; i < N1 * 3; i += NT) {
         const int c = i % 3;
-        stlev[i] = p.lev[(long)(i / 3) * kLevW + (c == 0 ? 7 : c == 1 ? 8 : 2)];
+        stlev[i] = p.lev[(long)(kst + i / 3) * kLevW + (c == 0 ? 7 : c == 1 ? 8 : 2)];
     }
     __syncthreads();
 
@@ -429,8 +437,30 @@ __device__ __forceinline__ void stage_body(const StageParams &p, const int tile,
 #pragma unroll
         for (int f = 0; f < 6; ++f) scarry[f * NCOL + tid] = T(0);
 
-    for (int s = tid; s < NSP; s += NT) stage(0, 0, s);
-    for (int ez = 0; ez < p.nelz; ++ez) {
+    if (SPLIT && ez0 > 0) {
+        // the element below: its own columns on its N lower levels, and its top
+        // level (this chunk's bottom) with the halo; then its contribution at
+        // that level, as the walk would have left it
+        for (int i = tid; i < N * NCOL; i += NT) stage(kst + i / NCOL, i / NCOL, i % NCOL);
+        for (int s = tid; s < NSP; s += NT) stage(ez0 * N, N, s);
+        for (int i = tid; i < N1 * 5; i += NT) {
+            const int c = i % 5;
+            slev[i] = p.lev[(long)(kst + i / 5) * kLevW + (c == 0 ? 0 : c + 2)];
+        }
+        __syncthreads();
+        if (tid < NCOL) {
+            T dt[6];
+            zderiv(ez0 - 1, N, tid % TX, tid / TX, T(p.hz2[ez0 - 1]), dt);
+            const T wlo = T(slev[N * 5 + 3]);
+#pragma unroll
+            for (int f = 0; f < 6; ++f) scarry[f * NCOL + tid] = wlo * dt[f];
+        }
+        fill_stlev(ez0 * N);
+        __syncthreads();
+    } else {
+        for (int s = tid; s < NSP; s += NT) stage(0, 0, s);
+    }
+    for (int ez = ez0; ez < ez1; ++ez) {
         for (int i = tid; i < N * NSP; i += NT) stage(ez * N + 1 + i / NSP, 1 + i / NSP, i % NSP);
         for (int i = tid; i < N1 * 5; i += NT) {
             const int c = i % 5;
@@ -462,10 +492,11 @@ __device__ __forceinline__ void stage_body(const StageParams &p, const int tile,
         }
         // EOS level data for the next element's staging (its reads of this
         // element's data finished before the barrier above)
-        if (ez + 1 < p.nelz) fill_stlev((ez + 1) * N);
+        if (ez + 1 < ez1) fill_stlev((ez + 1) * N);
         __syncthreads();
     }
     // top level: only the contribution of the element below
+    if (SPLIT && ez1 < p.nelz) return;   // the chunk above has this level as its bottom
     const int ktop = p.nz - 1;
     for (int col = tid; col < NCOL; col += NT) {
         const int tx = col % TX, ty = col / TX;
@@ -496,6 +527,17 @@ template <int N, int AX, int AY, typename T>
 __global__ void __launch_bounds__((StageShape<N, AX, AY>::NT)) stage_kernel(const StageParams p)
 {
     stage_body<N, AX, AY, T>(p, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x);
+}
+
+// The same stage with each column cut into `nchunk` runs of elements, for
+// lattices with too few tiles for the chip (split_plan): workgroup
+// chunk * tiles + tile, element run [chunk nelz / nchunk, (chunk + 1) nelz / nchunk).
+template <int N, int AX, int AY, typename T>
+__global__ void __launch_bounds__((StageShape<N, AX, AY>::NT)) stage_kernel_split(const StageParams p, int nchunk)
+{
+    const int nt = p.ntx * p.nty, b = xcd_tile(blockIdx.x, gridDim.x);
+    const int chunk = b / nt;
+    stage_body<N, AX, AY, T, true>(p, b % nt, threadIdx.x, chunk * p.nelz / nchunk, (chunk + 1) * p.nelz / nchunk);
 }
 
 // Batched form: the (instance, tile) items of an order group sit in one list
@@ -1212,8 +1254,104 @@ hipError_t launch_stage_batched(int N, int precision, int variant, const StagePa
     return hipGetLastError();
 }
 
+// Tile shapes of the split form per order: the three variants' (order 4: the
+// first two) and a small one of about 256 threads.
+#define NH_SPLIT_CASES(X)          \
+    X(2, 16, 4, 8, 8, 16, 8, 8, 4) \
+    X(3, 10, 3, 5, 5, 8, 4, 3, 3)  \
+    X(4, 8, 2, 4, 4, 4, 2, 2, 2)   \
+    X(5, 6, 1, 3, 2, 4, 2, 2, 1)   \
+    X(6, 4, 1, 2, 2, 3, 1, 1, 1)
+
+template <int N, int AX, int AY>
+static void launch_split_one(int precision, StageParams p, int nchunk, hipStream_t s)
+{
+    using S = StageShape<N, AX, AY>;
+    p.ntx = (p.nx + S::TX - 1) / S::TX;
+    p.nty = (p.ny + S::TY - 1) / S::TY;
+    const dim3 grid(p.ntx * p.nty * nchunk), block(S::NT);
+    if (precision == 0)
+        hipLaunchKernelGGL((stage_kernel_split<N, AX, AY, double>), grid, block, 0, s, p, nchunk);
+    else
+        hipLaunchKernelGGL((stage_kernel_split<N, AX, AY, float>), grid, block, 0, s, p, nchunk);
+}
+
+static void launch_split(int N, int precision, int shape, const StageParams &p, int nchunk, hipStream_t s)
+{
+    switch (N) {
+#define NH_SPLIT(NN, X0, Y0, X1, Y1, X2, Y2, X3, Y3)                               \
+    case NN:                                                                       \
+        if (shape == 0) launch_split_one<NN, X0, Y0>(precision, p, nchunk, s);     \
+        if (shape == 1) launch_split_one<NN, X1, Y1>(precision, p, nchunk, s);     \
+        if (shape == 2) launch_split_one<NN, X2, Y2>(precision, p, nchunk, s);     \
+        if (shape == 3) launch_split_one<NN, X3, Y3>(precision, p, nchunk, s);     \
+        break;
+        NH_SPLIT_CASES(NH_SPLIT)
+#undef NH_SPLIT
+    }
+}
+
+// Choice of tile shape and column split for a lattice (variant 0).  The walk
+// over a column is a chain: a workgroup takes tau microseconds per element
+// however idle the chip is, so lattices of less than a few hundred tiles are
+// bound by that chain and by the last, partly filled round of workgroups
+// (a 40 x 40 x 16 order-4 lattice has 100 tiles for 256 CUs: 100 us per launch,
+// 58 with two runs per column; the 4 x 4 x 4 one 27 us, 11 with small tiles
+// and a run per element; a 40 x 40 x 16 order-5 one 251 us, 168 with the 20 x 10
+// tile).  The estimate below reproduces a sweep over 20 lattices, four
+// shapes and the runs per column to about 10 % in order: tau is measured per
+// order and shape on lattices that leave the chip idle, a workgroup costs
+// 3.5 us beside its elements (tables, the element below) and a launch 3 us,
+// the elements take up to 15 % longer as the chip fills, and small
+// workgroups that share a CU finish in 0.8 of their time alone.  A plan other
+// than whole columns of shape 0 is taken where it gains 6 % or more: the
+// 512 x 512 x 81 and 256 x 256 x 41 lattices (1024 and 256 tiles) keep it.
+void stage_plan(int N, int nx, int ny, int nelz, int *shape, int *nchunk)
+{
+    static const double tau[5][4] = {{3.2, 3.7, 4.5, 3.0}, {5.7, 6.1, 6.1, 3.8}, {6.0, 7.3, 4.9, 4.6},
+                                     {6.9, 7.8, 8.7, 5.1}, {9.5, 11.0, 7.8, 5.2}};
+    static const int ax[5][8] = {
+#define NH_SPLIT_SIZES(NN, X0, Y0, X1, Y1, X2, Y2, X3, Y3) {X0, Y0, X1, Y1, X2, Y2, X3, Y3},
+        NH_SPLIT_CASES(NH_SPLIT_SIZES)
+#undef NH_SPLIT_SIZES
+    };
+    *shape = 0;
+    *nchunk = 1;
+    if (N < 2 || N > kMaxN) return;
+    double best = 0.0;
+    for (int s = 0; s < 4; ++s) {
+        const int tx = ax[N - 2][2 * s] * N, ty = ax[N - 2][2 * s + 1] * N;
+        const double tiles = (double)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+        for (int z = 1; z <= nelz; ++z) {
+            const int e = (nelz + z - 1) / z;                 // elements of the longest run
+            if (z > 1 && (nelz + z - 2) / (z - 1) == e) continue;   // as long with fewer runs
+            const double n = tiles * z, fill = n < 256.0 ? n / 256.0 : 1.0;
+            const double one = e * tau[N - 2][s] * (1.0 + 0.15 * fill) + 3.5;
+            double t;
+            if (s == 3) {
+                const double m = n / 256.0;                   // several to a CU
+                t = one > 0.8 * m * one ? one : 0.8 * m * one;
+            } else {
+                t = one * (double)((long)((n + 255.0) / 256.0));
+            }
+            t += 3.0;
+            if (s == 0 && z == 1) best = 0.94 * t;
+            else if (t < best) {
+                best = t;
+                *shape = s;
+                *nchunk = z;
+            }
+        }
+    }
+}
+
 hipError_t launch_stage(int N, int precision, int variant, const StageParams &p, hipStream_t s)
 {
+    if (variant == 0 && (p.shape != 0 || p.nchunk > 1)) {
+        if (p.nchunk < 1 || p.nchunk > p.nelz || p.shape < 0 || p.shape > 3) return hipErrorInvalidValue;
+        launch_split(N, precision, p.shape, p, p.nchunk, s);
+        return hipGetLastError();
+    }
     switch (N) {
 #define NH_LAUNCH(NN, AX0, AY0, AX1, AY1, AX2, AY2)                    \
     case NN:                                                           \

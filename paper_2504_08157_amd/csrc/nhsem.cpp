@@ -24,6 +24,7 @@ using namespace nh;
 
 struct nh_ctx {
     int N, nel[3], per[2], n[3], precision, tile;
+    int plan_shape, plan_chunks;        // stage launch of tile variant 0 (stage_plan)
     int64_t U, L;
     std::vector<double> xe, ye, ze;
     std::vector<double> xi, w, D;       // LGL basis
@@ -422,7 +423,9 @@ void hyper_rows(const nh_ctx *c, int nel, const double *edges, int periodic, con
 hipError_t run_stage(nh_ctx *c, double t, const double *qs, const double *qn, double *out, double a,
                      double b, double cc)
 {
-    const StageParams p = stage_params(c, t, qs, qn, out, a, b, cc);
+    StageParams p = stage_params(c, t, qs, qn, out, a, b, cc);
+    p.shape = c->plan_shape;
+    p.nchunk = c->plan_chunks;
     hipError_t e = launch_stage(c->N, c->precision, c->tile, p, c->stream);
     if (e == hipSuccess && c->hd_on) {
         // out += cc H(qs), H = -(div tau grad)^2 qs
@@ -543,6 +546,7 @@ nh_status nh_init_mesh(const nh_mesh_desc *mesh, const nh_physics *phys, void *d
         }
     }
 
+    stage_plan(c->N, c->n[0], c->n[1], c->nel[2], &c->plan_shape, &c->plan_chunks);
     hipStream_t s = c->stream;
     auto up = [&](void *dst, const void *src, size_t n) { return hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, s); };
     hipError_t e = hipSuccess;
