@@ -272,8 +272,6 @@ constexpr int kMlpMaxPasses = 4;   // network applications per initial guess, at
 constexpr int kMlpSlices = 16;  // batch slices of the weight-gradient GEMMs
 constexpr int kMlpNC = 65;     // canonical levels: LGL nodes of 16 order-4 elements
 constexpr int kMlpNF = 3 * kMlpNC;
-constexpr int kMlpLossBlocks = 256;
-constexpr int kMlpColRows = 64;    // rows per partial of the bias-gradient column sums
 
 struct MlpColParams {
     int nx, ny, nz;
@@ -290,8 +288,9 @@ struct MlpNet {
     const void *wh[4];             // FP16 weights inside `half` (W1, W2, W3, linear bypass S)
     float *b[3];                   // FP32 biases inside `master`
     float *gw[4], *gb[3];          // gradients inside `grad`
-    float *Z1, *Z2, *Y, *dY, *dH, *dZ, *part, *loss;
-    float *part_k;                 // [kMlpSlices][kMlpOut][kMlpIn] split-K partials
+    float *Z1, *Z2, *Y, *dY, *dZ2, *dZ1, *loss;
+    float *part;                   // loss partials, one per workgroup of the row part
+    float *part_k;                 // [kMlpSlices][nparam] partial gradients
     void *H1, *H2;                 // FP16 activations
     void *feat;                    // FP16 [max_batch][kMlpIn]
     double *scale;                 // [max_batch] column scales
@@ -323,7 +322,10 @@ hipError_t launch_mlp_guess(const MlpColParams &p, const double *b, long col0, l
                             const double *scale, double *x0, hipStream_t s);
 hipError_t mlp_forward(const MlpNet &net, int M, const void *X, hipStream_t s, bool keep_z = true);
 hipError_t mlp_backward(const MlpNet &net, int M, const void *X, const float *dY, hipStream_t s);
-hipError_t mlp_loss_grad(const MlpNet &net, int M, const float *T, float *loss, hipStream_t s);
+// forward, mean-squared-error loss against T (into net.loss and, if given,
+// loss2), backward, Adam
+hipError_t mlp_train_step(const MlpNet &net, int M, const void *X, const float *T, float lr, float b1, float b2,
+                          float eps, int step, float wd, float *loss2, hipStream_t s);
 // Adam step; wd > 0 adds decoupled weight decay on the hidden path's
 // parameters (W1, b1, W2, b2, W3, b3), not on the bypass S
 hipError_t mlp_adam(const MlpNet &net, float lr, float b1, float b2, float eps, int step, float wd, hipStream_t s);

@@ -629,68 +629,341 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) m
     }
 }
 
-// ---------------------------------------------------------------- backward (FP32 MFMA)
-// C[Mo x No] = sum_k A(mo, k) B(k, no) over k in [z kslice, (z + 1) kslice),
-// into C + z Mo No (split K; the slices are summed by sum_slices_kernel).
-// A is FP32 with element strides (sam, sak), B FP16 or FP32 with strides
-// (sbk, sbn).  FP32 products and accumulation on v_mfma_f32_16x16x4_f32
-// (lane l: A row l % 16 and B column l % 16 at k = l / 16; result rows
-// 4 (l / 16) + i, column l % 16).  Workgroup: a 64 x 64 tile, 4 waves of
-// 2 x 2 MFMA tiles (wave w: rows 32 (w / 2) .., columns 32 (w % 2) ..); K
-// staged through LDS in chunks of 32 as FP32, rows of kBkLd floats so that
-// the four k rows a wave reads at once fall in distinct banks.  Staging
-// walks whichever operand index has unit stride fastest (coalesced loads).
-constexpr int kBkK = 32, kBkLd = 80, kBkPer = kBkK * 64 / 256;
+// ---------------------------------------------------------------- training, row part
+// Everything of a training step that is local to a batch row, for R rows per
+// workgroup of 8 waves: the three layers (FWD; FP16 MFMA, the operands and the
+// order of accumulation of gemm_rows_kernel), the gradient of the mean squared
+// error dY = 2 (Y - T) / n with a loss partial per workgroup, and the chain
+//   dZ2 = (dY W3) SiLU'(Z2),   dZ1 = (dZ2 W2) SiLU'(Z1)
+// on v_mfma_f32_16x16x4_f32 (FP32 products and accumulation).  Without FWD
+// (nh_mlp_backward) dY, Z1 and Z2 are read instead of computed.  Written for the
+// weight gradients and for a later nh_mlp_backward: Z1, Z2, H1, H2, dY, dZ2,
+// dZ1.  Row tiles stay in LDS from layer to layer; wave w owns output columns
+// 32 w .. 32 w + 31, lane r16 of column tile c the column 32 w + 2 r16 + c, so that
+// a lane's two columns are one 8-byte access and the weights of the backward
+// products, stored with that index fastest, are read in pairs.  A wave loads a
+// layer's whole weight strip into registers (64 VGPRs) before it multiplies:
+// one exposed L2 latency per layer.
+// Bound: the FP32 products, 2 x 256 x 256 x 2 flops per row (13.7 us for 8192 rows
+// at the 157 TFLOP/s of the FP32 matrix units), and the layer-by-layer chain of two
+// waves per SIMD around them: 56 us for 8192 rows, where the separate products, SiLU
+// gradients and loss took 190 us (a training step of 8192 rows: 532 us before, 104 now).
+constexpr int kTrX = kMlpIn + 8;    // LDS row of the features (halves)
+constexpr int kTrH = kMlpHid + 8;   // LDS row of the activations (halves)
+constexpr int kTrD = kMlpHid + 4;   // LDS row of the FP32 gradients
 
-template <typename TB>
-__global__ void __launch_bounds__(256) gemm_mfma32_kernel(const float *__restrict__ A, long sam, long sak,
-                                                          const TB *__restrict__ B, long sbk, long sbn, int Mo,
-                                                          int No, int K, float *__restrict__ C, int kslice)
+// a caller's targets and output gradients are aligned to their elements only
+typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
+struct TrainRows {
+    const _Float16 *X;                       // [M][kMlpIn]
+    const float *T;                          // [M][kMlpOut] targets (FWD)
+    MlpWeights wt;
+    float *Z1, *Z2, *dY, *dZ2, *dZ1;         // [M][256]
+    _Float16 *H1, *H2;                       // [M][256]
+    const float *dYin;                       // the caller's dY (without FWD)
+    float *part;                             // [workgroups] loss partials (FWD)
+    float scale;                             // 1 / n of the loss
+};
+
+__device__ __forceinline__ float silu_grad(float z)
 {
-    __shared__ float As[kBkK][kBkLd];
-    __shared__ float Bs[kBkK][kBkLd];
-    const int t = threadIdx.x, wave = t / 64, lane = t % 64;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int kb = blockIdx.z * kslice, ke = min(K, kb + kslice);
-    C += (long)blockIdx.z * Mo * No;
-    const int wm = 32 * (wave / 2), wn = 32 * (wave % 2);
-    const int r16 = lane % 16, kq = lane / 16;
-    // staging slots of this thread: (k, m) of A and (k, n) of B for each of
-    // kBkPer values, the unit-stride index running fastest
-    int ka[kBkPer], ma[kBkPer], kbs[kBkPer], nb[kBkPer];
-#pragma unroll
-    for (int r = 0; r < kBkPer; ++r) {
-        const int i = t + r * 256;
-        ka[r] = sak == 1 ? i % kBkK : i / 64;
-        ma[r] = sak == 1 ? i / kBkK : i % 64;
-        kbs[r] = sbk == 1 ? i % kBkK : i / 64;
-        nb[r] = sbk == 1 ? i / kBkK : i % 64;
-    }
-    float ra[kBkPer], rb[kBkPer];
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int r = 0; r < kBkPer; ++r) {
-            const int gm = m0 + ma[r], gka = k0 + ka[r];
-            ra[r] = (gm < Mo && gka < ke) ? A[gm * sam + gka * sak] : 0.f;
-            const int gn = n0 + nb[r], gkb = k0 + kbs[r];
-            rb[r] = (gn < No && gkb < ke) ? (float)B[gkb * sbk + gn * sbn] : 0.f;
+    const float sg = 1.f / (1.f + expf(-z));
+    return sg * (1.f + z * (1.f - sg));
+}
+
+template <int R, bool FWD>
+__global__ void __launch_bounds__(512) mlp_train_rows_kernel(const TrainRows p)
+{
+    static_assert(kMlpHid == 256 && kMlpOut == 256 && (R == 16 || R == 32), "8 waves x 32 columns");
+    constexpr int RA = R / 16;
+    __shared__ __align__(16) _Float16 sX[FWD ? R * kTrX : 8];
+    __shared__ __align__(16) _Float16 sH[FWD ? R * kTrH : 8];
+    __shared__ __align__(16) float sD[R * kTrD];
+    __shared__ float sloss[8];
+    const int t = threadIdx.x, wave = t / 64, lane = t % 64, r16 = lane % 16, g = lane / 16;
+    const long m0 = (long)blockIdx.x * R;
+    const int n0 = 32 * wave + 2 * r16;   // the lane's columns n0, n0 + 1
+
+    float z1[RA][2][4], z2[RA][2][4];
+    if constexpr (FWD) {
+        for (int i = t; i < R * (kMlpIn / 8); i += 512) {
+            const int r = i / (kMlpIn / 8), o = i % (kMlpIn / 8);
+            *(half8 *)(sX + r * kTrX + 8 * o) = *(const half8 *)(p.X + (m0 + r) * kMlpIn + 8 * o);
         }
+        // weight strip of the wave: rows n0, n0 + 1 of W [256][KK]
+        constexpr int KX = kMlpIn / 32, KH = kMlpHid / 32;
+        static_assert(kMlpIn % 32 == 16 && kMlpHid % 32 == 0, "one 16-wide remainder in the feature layers");
+        auto load_h = [&](const _Float16 *W, half8 (&w8)[KH][2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < KH; ++k)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) w8[k][c] = *(const half8 *)(W + (long)(n0 + c) * kMlpHid + 32 * k + 8 * g);
+        };
+        auto load_x = [&](const _Float16 *W, half8 (&w8)[KX][2], half4 (&w4)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+#pragma unroll
+                for (int k = 0; k < KX; ++k) w8[k][c] = *(const half8 *)(W + (long)(n0 + c) * kMlpIn + 32 * k + 8 * g);
+                w4[c] = *(const half4 *)(W + (long)(n0 + c) * kMlpIn + 32 * KX + 4 * g);
+            }
+        };
+        auto mul_x = [&](const half8 (&w8)[KX][2], const half4 (&w4)[2], float4v (&acc)[RA][2])
+                         __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < KX; ++k)
+#pragma unroll
+                for (int a = 0; a < RA; ++a) {
+                    const half8 av = *(const half8 *)(sX + (16 * a + r16) * kTrX + 32 * k + 8 * g);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) acc[a][c] = mfma_k32(av, w8[k][c], acc[a][c]);
+                }
+#pragma unroll
+            for (int a = 0; a < RA; ++a) {
+                const half4 av = *(const half4 *)(sX + (16 * a + r16) * kTrX + 32 * KX + 4 * g);
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x16f16(av, w4[c], acc[a][c], 0, 0, 0);
+            }
+        };
+        auto mul_h = [&](const half8 (&w8)[KH][2], float4v (&acc)[RA][2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < KH; ++k)
+#pragma unroll
+                for (int a = 0; a < RA; ++a) {
+                    const half8 av = *(const half8 *)(sH + (16 * a + r16) * kTrH + 32 * k + 8 * g);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) acc[a][c] = mfma_k32(av, w8[k][c], acc[a][c]);
+                }
+        };
+        auto clear = [&](float4v (&acc)[RA][2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int a = 0; a < RA; ++a)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[a][c] = float4v{0.f, 0.f, 0.f, 0.f};
+        };
+        // z = acc + bias to registers and memory, SiLU(z) to LDS and memory
+        auto layer_out = [&](const float4v (&acc)[RA][2], const float *bias, float (&z)[RA][2][4], float *Z,
+                             _Float16 *Hg) __attribute__((always_inline)) {
+            const float b0 = bias[n0], b1 = bias[n0 + 1];
+#pragma unroll
+            for (int a = 0; a < RA; ++a)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = 16 * a + 4 * g + i;
+                    const float u = acc[a][0][i] + b0, v = acc[a][1][i] + b1;
+                    z[a][0][i] = u;
+                    z[a][1][i] = v;
+                    *(float2 *)(Z + (m0 + row) * 256 + n0) = make_float2(u, v);
+                    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+                    const half2v h = {(_Float16)(u / (1.0f + expf(-u))), (_Float16)(v / (1.0f + expf(-v)))};
+                    *(half2v *)(sH + row * kTrH + n0) = h;
+                    *(half2v *)(Hg + (m0 + row) * 256 + n0) = h;
+                }
+        };
+        float4v acc[RA][2], acc3[RA][2];
+        clear(acc);
+        clear(acc3);
+        half8 wa[KX][2], wb[KX][2], wh[KH][2];
+        half4 wa4[2], wb4[2];
+        load_x(p.wt.W[0], wa, wa4);
+        load_x(p.wt.W[3], wb, wb4);
+        __syncthreads();
+        mul_x(wa, wa4, acc);
+        load_h(p.wt.W[1], wh);
+        mul_x(wb, wb4, acc3);   // the bypass is accumulated first
+        layer_out(acc, p.wt.bias[0], z1, p.Z1, p.H1);
+        __syncthreads();
+        clear(acc);
+        mul_h(wh, acc);
+        load_h(p.wt.W[2], wh);
+        __syncthreads();        // every wave has read H1
+        layer_out(acc, p.wt.bias[1], z2, p.Z2, p.H2);
+        __syncthreads();
+        mul_h(wh, acc3);
+        float loss = 0.f;
+        {
+            const float b0 = p.wt.bias[2][n0], b1 = p.wt.bias[2][n0 + 1];
+#pragma unroll
+            for (int a = 0; a < RA; ++a)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int row = 16 * a + 4 * g + i;
+                    const float2u tt = *(const float2u *)(p.T + (m0 + row) * 256 + n0);
+                    const float d0 = (acc3[a][0][i] + b0) - tt.x, d1 = (acc3[a][1][i] + b1) - tt.y;
+                    loss += d0 * d0 + d1 * d1;
+                    const float2 dy = make_float2(2.f * d0 * p.scale, 2.f * d1 * p.scale);
+                    *(float2 *)(sD + row * kTrD + n0) = dy;
+                    *(float2 *)(p.dY + (m0 + row) * 256 + n0) = dy;
+                }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o);
+        if (lane == 0) sloss[wave] = loss;
+        __syncthreads();
+        if (t == 0) {
+            float l = 0.f;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) l += sloss[w];
+            p.part[blockIdx.x] = l;
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 16 * a + 4 * g + i;
+                const long o = (m0 + row) * 256 + n0;
+                const float2 u = *(const float2 *)(p.Z1 + o), v = *(const float2 *)(p.Z2 + o);
+                z1[a][0][i] = u.x;
+                z1[a][1][i] = u.y;
+                z2[a][0][i] = v.x;
+                z2[a][1][i] = v.y;
+                const float2u dy = *(const float2u *)(p.dYin + o);
+                *(float2 *)(sD + row * kTrD + n0) = make_float2(dy.x, dy.y);
+            }
+        __syncthreads();
+    }
+
+    // acc[m][n] = sum_k sD[m][k] W[k][n], W [256][256] FP16 with n fastest: in
+    // each block of 16 k, lane quarter g holds k = 4 g + i for the i-th product
+    // (the same k in both operands)
+    auto chain = [&](const _Float16 *W, float4v (&acc)[RA][2]) __attribute__((always_inline)) {
+        typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[a][c] = float4v{0.f, 0.f, 0.f, 0.f};
+        constexpr int KB = 8;   // blocks of 16 k whose weights are in registers at a time
+        half2v w[KB][4];
+        auto load = [&](int kb0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int b = 0; b < KB; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    w[b][i] = *(const half2v *)(W + (long)(16 * (kb0 + b) + 4 * g + i) * 256 + n0);
+        };
+        load(0);
+#pragma unroll
+        for (int kb0 = 0; kb0 < 16; kb0 += KB) {
+#pragma unroll
+            for (int b = 0; b < KB; ++b) {
+                float4v av[RA];
+#pragma unroll
+                for (int a = 0; a < RA; ++a)
+                    av[a] = *(const float4v *)(sD + (16 * a + r16) * kTrD + 16 * (kb0 + b) + 4 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+#pragma unroll
+                        for (int a = 0; a < RA; ++a)
+                            acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a][i], (float)w[b][i][c], acc[a][c],
+                                                                             0, 0, 0);
+            }
+            if (kb0 + KB < 16) load(kb0 + KB);
+        }
+    };
+    float4v d[RA][2];
+    chain(p.wt.W[2], d);
+    __syncthreads();   // every wave has read dY
+#pragma unroll
+    for (int a = 0; a < RA; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 16 * a + 4 * g + i;
+            const float2 dz = make_float2(d[a][0][i] * silu_grad(z2[a][0][i]), d[a][1][i] * silu_grad(z2[a][1][i]));
+            *(float2 *)(sD + row * kTrD + n0) = dz;
+            *(float2 *)(p.dZ2 + (m0 + row) * 256 + n0) = dz;
+        }
+    __syncthreads();
+    chain(p.wt.W[1], d);
+#pragma unroll
+    for (int a = 0; a < RA; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 16 * a + 4 * g + i;
+            *(float2 *)(p.dZ1 + (m0 + row) * 256 + n0) =
+                make_float2(d[a][0][i] * silu_grad(z1[a][0][i]), d[a][1][i] * silu_grad(z1[a][1][i]));
+        }
+}
+
+// ---------------------------------------------------------------- training, batch sums
+// The four weight gradients and three bias gradients in one launch:
+//   dS = dY^T X, dW3 = dY^T H2, dW2 = dZ2^T H1, dW1 = dZ1^T X, db = column sums,
+// FP32 products and accumulation on v_mfma_f32_16x16x4_f32 (lane l: A row l % 16 and
+// B column l % 16 at k = l / 16).  Workgroup: a 64 x 64 tile of one gradient over
+// one slice of the batch, 4 waves of 2 x 2 MFMA tiles; chunks of 32 batch rows go
+// through LDS as FP32, the next chunk in registers during the products; rows of
+// kBkLd floats so that the four k rows a wave reads fall in distinct banks.
+// The workgroups of a gradient's first column tile also sum the columns of A.
+// Slice z writes its share of the whole gradient vector to part + z nparam;
+// train_update_kernel adds the slices in order (deterministic).
+// One launch instead of four (and no separate column sums) keeps up to 1024
+// workgroups in flight, four to a CU, which is what hides the staging latency.
+// 3.9 GFLOP at 8192 rows, 25 us at 157 TFLOP/s: 48 us measured (seven launches with
+// their sums and the column sums took 330 us).
+constexpr int kBkK = 32, kBkLd = 80;
+constexpr int kGradTiles = 4 * 16;   // 4 x 4 tiles of 64 x 64 per gradient (the last column tile of 208 is partial)
+
+struct GradJob {
+    const float *A;        // [M][256]
+    const _Float16 *B;     // [M][No]
+    int No;
+    long off, boff;        // offsets of the gradient and of the bias gradient (-1: none) in the parameter vector
+};
+struct GradJobs {
+    GradJob j[4];
+};
+
+__global__ void __launch_bounds__(256) mlp_grads_kernel(const GradJobs jobs, int M, int kslice, long nparam,
+                                                        float *__restrict__ part)
+{
+    __shared__ __align__(16) float As[kBkK][kBkLd];
+    __shared__ __align__(16) float Bs[kBkK][kBkLd];
+    const int t = threadIdx.x, wave = t / 64, lane = t % 64, r16 = lane % 16, kq = lane / 16;
+    const GradJob J = jobs.j[blockIdx.x / 16];
+    const int m0 = 64 * ((blockIdx.x % 16) / 4), n0 = 64 * (blockIdx.x % 4);
+    const int kb = blockIdx.y * kslice, ke = min(M, kb + kslice);   // kslice and M are multiples of 32
+    float *out = part + (long)blockIdx.y * nparam;
+    const int wm = 32 * (wave / 2), wn = 32 * (wave % 2);
+    const bool bias = J.boff >= 0 && n0 == 0;
+    // staging: A rows t / 16 and t / 16 + 16, four columns; B row t / 8, eight columns
+    const float *ga = J.A + m0 + 4 * (t % 16);
+    const bool bin = n0 + 8 * (t % 8) < J.No;
+    const _Float16 *gb = J.B + (bin ? n0 + 8 * (t % 8) : 0);
+    float4v ra[2];
+    half8 rb;
+    auto load = [&](int k0) __attribute__((always_inline)) {
+        ra[0] = *(const float4u *)(ga + (long)(k0 + t / 16) * 256);
+        ra[1] = *(const float4u *)(ga + (long)(k0 + 16 + t / 16) * 256);
+        rb = *(const half8 *)(gb + (long)(k0 + t / 8) * J.No);
     };
     float4v acc[2][2];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int y = 0; y < 2; ++y) acc[x][y] = float4v{0.f, 0.f, 0.f, 0.f};
-    load(kb);
+    float bsum = 0.f;
+    if (kb < ke) load(kb);
     for (int k0 = kb; k0 < ke; k0 += kBkK) {
         __syncthreads();   // the previous chunk has been read
+        *(float4v *)&As[t / 16][4 * (t % 16)] = ra[0];
+        *(float4v *)&As[16 + t / 16][4 * (t % 16)] = ra[1];
+        float4v b0, b1;
 #pragma unroll
-        for (int r = 0; r < kBkPer; ++r) {
-            As[ka[r]][ma[r]] = ra[r];
-            Bs[kbs[r]][nb[r]] = rb[r];
+        for (int i = 0; i < 4; ++i) {
+            b0[i] = bin ? (float)rb[i] : 0.f;
+            b1[i] = bin ? (float)rb[4 + i] : 0.f;
         }
+        *(float4v *)&Bs[t / 8][8 * (t % 8)] = b0;
+        *(float4v *)&Bs[t / 8][8 * (t % 8) + 4] = b1;
         __syncthreads();
-        if (k0 + kBkK < ke) load(k0 + kBkK);   // next chunk in flight during the products
+        if (k0 + kBkK < ke) load(k0 + kBkK);
+        if (bias)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) bsum += As[8 * wave + i][lane];
 #pragma unroll
         for (int kk = 0; kk < kBkK; kk += 4) {
             float a[2], b[2];
@@ -702,7 +975,8 @@ __global__ void __launch_bounds__(256) gemm_mfma32_kernel(const float *__restric
 #pragma unroll
             for (int x = 0; x < 2; ++x)
 #pragma unroll
-                for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x], b[y], acc[x][y], 0, 0, 0);
+                for (int y = 0; y < 2; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x], b[y], acc[x][y], 0, 0, 0);
         }
     }
 #pragma unroll
@@ -712,102 +986,77 @@ __global__ void __launch_bounds__(256) gemm_mfma32_kernel(const float *__restric
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int row = m0 + wm + 16 * x + 4 * kq + i, col = n0 + wn + 16 * y + r16;
-                if (row < Mo && col < No) C[(long)row * No + col] = acc[x][y][i];
+                if (col < J.No) out[J.off + (long)row * J.No + col] = acc[x][y][i];
             }
-}
-
-// out[i] = sum_z P[z][i], z = 0 .. slices-1 in order (deterministic)
-__global__ void sum_slices_kernel(const float *__restrict__ P, int slices, long n, float *__restrict__ out)
-{
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        float t = 0.f;
-        for (int z = 0; z < slices; ++z) t += P[z * n + i];
-        out[i] = t;
-    }
-}
-
-// column sums of X [M][N] over row chunks of kMlpColRows: part[c][n] = sum over
-// rows m of chunk c of X[m][n].  Workgroup of 256 threads = 64 columns x 4
-// row phases (coalesced 256-byte row segments); the 4 phase sums of a column
-// are added in a fixed order, and sum_slices_kernel adds the chunks in
-// order, so the result is deterministic.
-__global__ void __launch_bounds__(256) colsum_part_kernel(const float *__restrict__ X, int M, int N,
-                                                          float *__restrict__ part)
-{
-    __shared__ float ph[4][64];
-    const int c = threadIdx.x % 64, r = threadIdx.x / 64;
-    const int n = blockIdx.x * 64 + c;
-    const int m0 = blockIdx.y * kMlpColRows, m1 = min(M, m0 + kMlpColRows);
-    float s = 0.f;
-    if (n < N)
-        for (int m = m0 + r; m < m1; m += 4) s += X[(long)m * N + n];
-    ph[r][c] = s;
-    __syncthreads();
-    if (r == 0 && n < N) part[(long)blockIdx.y * N + n] = ((ph[0][c] + ph[1][c]) + ph[2][c]) + ph[3][c];
-}
-
-// dY = 2 (Y - T) / (M N), loss partials per block
-__global__ void mse_grad_kernel(const float *__restrict__ Y, const float *__restrict__ T, long n, float scale,
-                                float *__restrict__ dY, float *__restrict__ part)
-{
-    __shared__ float sh[256];
-    float a = 0.f;
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        const float d = Y[i] - T[i];
-        dY[i] = 2.f * d * scale;
-        a += d * d;
-    }
-    sh[threadIdx.x] = a;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
+    if (bias) {
+        __syncthreads();   // As has been read
+        As[wave][lane] = bsum;
         __syncthreads();
+        if (wave == 0) out[J.boff + m0 + lane] = ((As[0][lane] + As[1][lane]) + As[2][lane]) + As[3][lane];
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-// *out = scale * sum of part[0 .. n): one wave, lane l the entries l, l + 64,
-// ... in order, then a fixed butterfly
-__global__ void __launch_bounds__(64) sum_kernel(const float *__restrict__ part, int n, float scale,
-                                                 float *__restrict__ out)
+struct AdamArgs {
+    float *w, *m, *v;
+    _Float16 *wh;
+    float lr, b1, b2, eps, c1, c2;
+    long ndecay;
+    float wd;
+};
+
+__device__ __forceinline__ void adam_update(const AdamArgs &a, long i, float gi)
 {
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n; i += 64) s += part[i];
+    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    float u = (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+    if (i < a.ndecay) u += a.wd * a.w[i];
+    const float wi = a.w[i] - a.lr * u;
+    a.w[i] = wi;
+    a.wh[i] = (_Float16)wi;
+}
+
+// g = the slices of part added in order; with ADAM the update with it; and, in
+// the first workgroup, the loss: scale times the sum of its nloss partials
+// (lane l the entries l, l + 64, ... in order, then a fixed butterfly).
+template <bool ADAM>
+__global__ void __launch_bounds__(256) train_update_kernel(long n, const float *__restrict__ part, int slices,
+                                                           float *__restrict__ grad, const AdamArgs a,
+                                                           const float *__restrict__ lpart, int nloss, float scale,
+                                                           float *__restrict__ loss, float *__restrict__ loss2)
+{
+    const long i = blockIdx.x * 256L + threadIdx.x;
+    if (ADAM && blockIdx.x == 0 && threadIdx.x < 64) {
+        float l = 0.f;
+        for (int k = threadIdx.x; k < nloss; k += 64) l += lpart[k];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (threadIdx.x == 0) *out = s * scale;
-}
-
-// dZ = dH * SiLU'(Z),  SiLU'(z) = sig(z) (1 + z (1 - sig(z)))
-__global__ void silu_back_kernel(const float *__restrict__ dH, const float *__restrict__ Z, long n,
-                                 float *__restrict__ dZ)
-{
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        const float z = Z[i];
-        const float sg = 1.f / (1.f + expf(-z));
-        dZ[i] = dH[i] * sg * (1.f + z * (1.f - sg));
+        for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+        if (threadIdx.x == 0) {
+            *loss = l * scale;
+            if (loss2) *loss2 = l * scale;
+        }
     }
+    if (i >= n) return;
+    float s = 0.f;
+    int z = 0;
+    for (; z + 4 <= slices; z += 4) {
+        const float p0 = part[z * n + i], p1 = part[(z + 1) * n + i], p2 = part[(z + 2) * n + i],
+                    p3 = part[(z + 3) * n + i];
+        s = (((s + p0) + p1) + p2) + p3;
+    }
+    for (; z < slices; ++z) s += part[z * n + i];
+    grad[i] = s;
+    if constexpr (ADAM) adam_update(a, i, s);
 }
 
 // Adam on FP32 masters (Kingma & Ba), then FP16 copies.  The first ndecay
 // parameters also take decoupled weight decay wd (Loshchilov & Hutter):
 // w -= lr (m_hat / (sqrt(v_hat) + eps) + wd w).
-__global__ void adam_kernel(long n, const float *__restrict__ g, float *__restrict__ w, float *__restrict__ m,
-                            float *__restrict__ v, _Float16 *__restrict__ wh, float lr, float b1, float b2,
-                            float eps, float c1, float c2, long ndecay, float wd)
+__global__ void adam_kernel(long n, const float *__restrict__ g, const AdamArgs a)
 {
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.f - b1) * gi;
-        const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        float u = (mi / c1) / (sqrtf(vi / c2) + eps);
-        if (i < ndecay) u += wd * w[i];
-        const float wi = w[i] - lr * u;
-        w[i] = wi;
-        wh[i] = (_Float16)wi;
-    }
+    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
+        adam_update(a, i, g[i]);
 }
 
 __global__ void to_half_kernel(long n, const float *__restrict__ w, _Float16 *__restrict__ wh)
@@ -890,75 +1139,106 @@ hipError_t mlp_forward(const MlpNet &net, int M, const void *X, hipStream_t s, b
     return hipGetLastError();
 }
 
-// Weight gradient G[Mo x No] = sum over the batch (K = M rows) of A^T B,
-// split over the batch so that enough workgroups run (a 256 x 208 gradient
-// is only 28 tiles), then the slices are summed in a fixed order.
-template <typename TB>
-static void weight_grad(const float *A, long lda, const TB *B, long ldb, int Mo, int No, int K, float *G,
-                        float *part, hipStream_t s)
+// Rows per workgroup of the row part: 32 (the weights of each layer are read
+// once per 32 rows), 16 while that does not give each CU two workgroups.  A
+// training step with 16 and with 32 rows: 46.2 and 59.7 us (batch 1024), 61.0 and
+// 73.8 (4096), 97.6 and 86.4 (6144), 107.7 and 99.0 (8192).
+static int train_rows(int M) { return M > 4096 ? 32 : 16; }
+
+template <bool FWD>
+static void launch_train_rows(const TrainRows &r, int M, hipStream_t s)
 {
-    int slices = K / 64;
-    if (slices > kMlpSlices) slices = kMlpSlices;
-    if (slices < 1) slices = 1;
-    const int kslice = (K + slices - 1) / slices;
-    hipLaunchKernelGGL((gemm_mfma32_kernel<TB>), dim3((No + 63) / 64, (Mo + 63) / 64, slices), dim3(256), 0, s,
-                       A, 1L, lda, B, ldb, 1L, Mo, No, K, part, kslice);
-    const long n = (long)Mo * No;
-    hipLaunchKernelGGL(sum_slices_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, part, slices, n, G);
+    if (train_rows(M) == 32)
+        hipLaunchKernelGGL((mlp_train_rows_kernel<32, FWD>), dim3(M / 32), dim3(512), 0, s, r);
+    else
+        hipLaunchKernelGGL((mlp_train_rows_kernel<16, FWD>), dim3(M / 16), dim3(512), 0, s, r);
 }
 
-// out[n] = sum over the M rows of X[m][n], through row-chunk partials in part
-static void column_sums(const float *X, int M, int N, float *out, float *part, hipStream_t s)
+static TrainRows train_rows_args(const MlpNet &net, const void *X)
 {
-    const int chunks = (M + kMlpColRows - 1) / kMlpColRows;
-    hipLaunchKernelGGL(colsum_part_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, s, X, M, N, part);
-    const long n = N;
-    hipLaunchKernelGGL(sum_slices_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, part, chunks, n, out);
+    TrainRows r{};
+    r.X = (const _Float16 *)X;
+    for (int i = 0; i < 4; ++i) r.wt.W[i] = (const _Float16 *)net.wh[i];
+    for (int i = 0; i < 3; ++i) r.wt.bias[i] = net.b[i];
+    r.Z1 = net.Z1; r.Z2 = net.Z2; r.dY = net.dY; r.dZ2 = net.dZ2; r.dZ1 = net.dZ1;
+    r.H1 = (_Float16 *)net.H1; r.H2 = (_Float16 *)net.H2;
+    r.part = net.part;
+    return r;
+}
+
+// Batch slices of the weight gradients: 128 rows or more each, at most
+// kMlpSlices (the partial sums of 16 slices are 15 MB).  A training step with
+// slices of 64, 128 and 256 rows: 38.4, 39.0 and 41.8 us (batch 256), 48.3, 46.2
+// and 45.7 (1024), no difference from 4096 on.
+static int grad_slices(int M)
+{
+    const int n = M / 128;
+    return n < 1 ? 1 : n > kMlpSlices ? kMlpSlices : n;
+}
+
+static hipError_t weight_grads(const MlpNet &net, int M, const void *X, const float *dY, int slices, hipStream_t s)
+{
+    const _Float16 *Xh = (const _Float16 *)X;
+    auto off = [&](const float *p) { return (long)(p - net.grad); };
+    GradJobs j;
+    j.j[0] = {dY, Xh, kMlpIn, off(net.gw[3]), -1};
+    j.j[1] = {dY, (const _Float16 *)net.H2, kMlpHid, off(net.gw[2]), off(net.gb[2])};
+    j.j[2] = {net.dZ2, (const _Float16 *)net.H1, kMlpHid, off(net.gw[1]), off(net.gb[1])};
+    j.j[3] = {net.dZ1, Xh, kMlpIn, off(net.gw[0]), off(net.gb[0])};
+    const int kslice = ((M + slices - 1) / slices + kBkK - 1) / kBkK * kBkK;
+    hipLaunchKernelGGL(mlp_grads_kernel, dim3(kGradTiles, slices), dim3(256), 0, s, j, M, kslice, net.nparam,
+                       net.part_k);
+    return hipGetLastError();
+}
+
+static AdamArgs adam_args(const MlpNet &net, float lr, float b1, float b2, float eps, int step, float wd)
+{
+    AdamArgs a{};
+    a.w = net.master; a.m = net.m; a.v = net.v; a.wh = (_Float16 *)net.half;
+    a.lr = lr; a.b1 = b1; a.b2 = b2; a.eps = eps;
+    a.c1 = 1.f - powf(b1, (float)step);
+    a.c2 = 1.f - powf(b2, (float)step);
+    // the hidden path (W1, b1, W2, b2, W3, b3) precedes the bypass S
+    a.ndecay = wd > 0.f ? net.nparam - (long)kMlpOut * kMlpIn : 0;
+    a.wd = wd;
+    return a;
 }
 
 hipError_t mlp_backward(const MlpNet &net, int M, const void *X, const float *dY, hipStream_t s)
 {
-    const dim3 blk(256);
-    const _Float16 *Xh = (const _Float16 *)X, *H1 = (const _Float16 *)net.H1, *H2 = (const _Float16 *)net.H2;
-    const _Float16 *W2 = (const _Float16 *)net.wh[1], *W3 = (const _Float16 *)net.wh[2];
-    // linear bypass: dS = dY^T X [256 x 208]
-    weight_grad(dY, (long)kMlpOut, Xh, (long)kMlpIn, kMlpOut, kMlpIn, M, net.gw[3], net.part_k, s);
-    // layer 3: dW3 = dY^T H2 [256 x 256], db3 = sum dY, dH2 = dY W3 [M x 256]
-    weight_grad(dY, (long)kMlpOut, H2, (long)kMlpHid, kMlpOut, kMlpHid, M, net.gw[2], net.part_k, s);
-    column_sums(dY, M, kMlpOut, net.gb[2], net.part_k, s);
-    hipLaunchKernelGGL((gemm_mfma32_kernel<_Float16>), dim3(kMlpHid / 64, M / 64, 1), blk, 0, s, dY,
-                       (long)kMlpOut, 1L, W3, (long)kMlpHid, 1L, M, kMlpHid, kMlpOut, net.dH, kMlpOut);
-    hipLaunchKernelGGL(silu_back_kernel, dim3(grid_for((long)M * kMlpHid, 256)), blk, 0, s, net.dH, net.Z2,
-                       (long)M * kMlpHid, net.dZ);
-    // layer 2
-    weight_grad(net.dZ, (long)kMlpHid, H1, (long)kMlpHid, kMlpHid, kMlpHid, M, net.gw[1], net.part_k, s);
-    column_sums(net.dZ, M, kMlpHid, net.gb[1], net.part_k, s);
-    hipLaunchKernelGGL((gemm_mfma32_kernel<_Float16>), dim3(kMlpHid / 64, M / 64, 1), blk, 0, s, net.dZ,
-                       (long)kMlpHid, 1L, W2, (long)kMlpHid, 1L, M, kMlpHid, kMlpHid, net.dH, kMlpHid);
-    hipLaunchKernelGGL(silu_back_kernel, dim3(grid_for((long)M * kMlpHid, 256)), blk, 0, s, net.dH, net.Z1,
-                       (long)M * kMlpHid, net.dZ);
-    // layer 1: dW1 = dZ1^T X [256 x K0]
-    weight_grad(net.dZ, (long)kMlpHid, Xh, (long)kMlpIn, kMlpHid, kMlpIn, M, net.gw[0], net.part_k, s);
-    column_sums(net.dZ, M, kMlpHid, net.gb[0], net.part_k, s);
+    TrainRows r = train_rows_args(net, X);
+    r.dYin = dY;
+    launch_train_rows<false>(r, M, s);
+    const int slices = grad_slices(M);
+    hipError_t e = weight_grads(net, M, X, dY, slices, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((train_update_kernel<false>), dim3((unsigned)((net.nparam + 255) / 256)), dim3(256), 0, s,
+                       net.nparam, net.part_k, slices, net.grad, AdamArgs{}, nullptr, 0, 0.f, nullptr, nullptr);
     return hipGetLastError();
 }
 
-hipError_t mlp_loss_grad(const MlpNet &net, int M, const float *T, float *loss, hipStream_t s)
+// One training step in three launches: everything local to a row, the weight
+// gradients, their sums with the Adam update and the loss.
+hipError_t mlp_train_step(const MlpNet &net, int M, const void *X, const float *T, float lr, float b1, float b2,
+                          float eps, int step, float wd, float *loss2, hipStream_t s)
 {
-    const long n = (long)M * kMlpOut;
-    hipLaunchKernelGGL(mse_grad_kernel, dim3(kMlpLossBlocks), dim3(256), 0, s, net.Y, T, n, 1.0f / (float)n, net.dY,
-                       net.part);
-    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(64), 0, s, net.part, kMlpLossBlocks, 1.0f / (float)n, loss);
+    TrainRows r = train_rows_args(net, X);
+    r.T = T;
+    r.scale = 1.0f / ((float)M * kMlpOut);
+    launch_train_rows<true>(r, M, s);
+    const int slices = grad_slices(M);
+    hipError_t e = weight_grads(net, M, X, net.dY, slices, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((train_update_kernel<true>), dim3((unsigned)((net.nparam + 255) / 256)), dim3(256), 0, s,
+                       net.nparam, net.part_k, slices, net.grad, adam_args(net, lr, b1, b2, eps, step, wd), net.part,
+                       M / train_rows(M), r.scale, net.loss, loss2);
     return hipGetLastError();
 }
 
 hipError_t mlp_adam(const MlpNet &net, float lr, float b1, float b2, float eps, int step, float wd, hipStream_t s)
 {
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    // the hidden path (W1, b1, W2, b2, W3, b3) precedes the bypass S
-    const long ndecay = wd > 0.f ? net.nparam - (long)kMlpOut * kMlpIn : 0;
     hipLaunchKernelGGL(adam_kernel, dim3(grid_for(net.nparam, 256)), dim3(256), 0, s, net.nparam, net.grad,
-                       net.master, net.m, net.v, (_Float16 *)net.half, lr, b1, b2, eps, c1, c2, ndecay, wd);
+                       adam_args(net, lr, b1, b2, eps, step, wd));
     return hipGetLastError();
 }
 

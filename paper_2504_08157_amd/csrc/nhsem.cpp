@@ -1456,16 +1456,13 @@ MlpLayout mlp_layout(long B)
     L.acts[1] = take(sizeof(float) * B * kMlpHid);     // Z2
     L.acts[2] = take(sizeof(float) * B * kMlpOut);     // Y
     L.acts[3] = take(sizeof(float) * B * kMlpOut);     // dY
-    L.acts[4] = take(sizeof(float) * B * kMlpHid);     // dH
-    L.acts[5] = take(sizeof(float) * B * kMlpHid);     // dZ
-    L.acts[6] = take(sizeof(float) * kMlpLossBlocks);  // part
+    L.acts[4] = take(sizeof(float) * B * kMlpHid);     // dZ2
+    L.acts[5] = take(sizeof(float) * B * kMlpHid);     // dZ1
+    L.acts[6] = take(sizeof(float) * (B / 16));        // loss partials
     L.acts[7] = take(sizeof(float) * 4);               // loss
     L.acts[8] = take(sizeof(uint16_t) * B * kMlpHid);  // H1
     L.acts[9] = take(sizeof(uint16_t) * B * kMlpHid);  // H2
-    // split-K partials of the weight gradients, and the row-chunk partials
-    // of the bias gradients
-    const size_t colsum_part = (size_t)((B + kMlpColRows - 1) / kMlpColRows) * kMlpOut;
-    L.acts[10] = take(sizeof(float) * std::max<size_t>((size_t)kMlpSlices * kMlpOut * kMlpIn, colsum_part));
+    L.acts[10] = take(sizeof(float) * kMlpSlices * np);   // partial gradients of the batch slices
     L.feat = take(sizeof(uint16_t) * B * kMlpIn);
     L.scale = take(sizeof(double) * B);
     L.total = off;
@@ -1612,7 +1609,7 @@ nh_status nh_mlp_create(int64_t max_batch, uint64_t seed, void *dev_ws, size_t b
     n.wh[3] = (const char *)n.half + sizeof(uint16_t) * offS;
     n.gw[3] = n.grad + offS;
     n.Z1 = (float *)(w + L.acts[0]); n.Z2 = (float *)(w + L.acts[1]); n.Y = (float *)(w + L.acts[2]);
-    n.dY = (float *)(w + L.acts[3]); n.dH = (float *)(w + L.acts[4]); n.dZ = (float *)(w + L.acts[5]);
+    n.dY = (float *)(w + L.acts[3]); n.dZ2 = (float *)(w + L.acts[4]); n.dZ1 = (float *)(w + L.acts[5]);
     n.part = (float *)(w + L.acts[6]); n.loss = (float *)(w + L.acts[7]);
     n.H1 = w + L.acts[8]; n.H2 = w + L.acts[9];
     n.part_k = (float *)(w + L.acts[10]);
@@ -1668,13 +1665,8 @@ nh_status nh_mlp_train_step(nh_mlp *m, int64_t batch, const void *dev_x_f16, con
     if (!(lr > 0) || !(b1 >= 0 && b1 < 1) || !(b2 >= 0 && b2 < 1) || !(eps > 0))
         return mfail(m, NH_EINVAL, "bad Adam hyper-parameters");
     const int M = (int)batch;
-    MLPCHK(m, mlp_forward(m->net, M, dev_x_f16, m->stream));
-    MLPCHK(m, mlp_loss_grad(m->net, M, dev_t, m->net.loss, m->stream));
-    MLPCHK(m, mlp_backward(m->net, M, dev_x_f16, m->net.dY, m->stream));
     ++m->step;
-    MLPCHK(m, mlp_adam(m->net, lr, b1, b2, eps, m->step, m->decay, m->stream));
-    if (dev_loss)
-        MLPCHK(m, hipMemcpyAsync(dev_loss, m->net.loss, sizeof(float), hipMemcpyDeviceToDevice, m->stream));
+    MLPCHK(m, mlp_train_step(m->net, M, dev_x_f16, dev_t, lr, b1, b2, eps, m->step, m->decay, dev_loss, m->stream));
     return NH_OK;
 }
 
