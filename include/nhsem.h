@@ -284,9 +284,9 @@ typedef struct {
                                  (NH_EUNSUPPORTED otherwise) */
     int32_t precondition;     /* global (3D-IMEX) solves only, ignored by the
                                  column solves: 1 = right-precondition with the
-                                 column systems (I - alpha L_v), solved by the
-                                 column GMRES(10) to rtol 1e-6 (flexible GMRES:
-                                 the preconditioned vectors are kept) */
+                                 column systems (I - alpha L_v), solved directly
+                                 (flexible GMRES: the preconditioned vectors are
+                                 kept) */
     int32_t guess_pick;       /* column solves started from a given guess (dev_x0,
                                  or the MLP guess of nh_hevi_step), restart 10 forms:
                                  1 = per column, compare the residual of the guess
@@ -361,7 +361,8 @@ nh_status nh_hevi_last_solves(nh_ctx *ctx, const double **R2, const double **X2,
 /* Device workspace of nh_global_solve and nh_imex3d_step for a restart
    length (restart + 1 Krylov vectors, restart preconditioned vectors, one
    scratch vector and, for the step, eight state-sized arrays, 5U doubles
-   each; plus the block partial sums and the solver's device state). */
+   each; plus the block partial sums, the solver's device state and the
+   operands of the column preconditioner). */
 nh_status nh_imex3d_workspace_bytes(const nh_ctx *ctx, int32_t restart, size_t *bytes);
 
 /* dev_y = L dev_x on device [5][U] arrays (distinct; NH_EINVAL otherwise or

@@ -687,7 +687,6 @@ template <int N, bool FULL, int M, int VR>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 gmres_elem_kernel(const HeviParams h, const GmresArgs g, const int ngrp)
 {
-    if (g.gate && *g.gate == 0) return;
     using Op = ElemOp<N, FULL>;
     constexpr int S = Op::S, ML = M > VR ? M - VR : 0;
     __shared__ double sc[Op::NC][kColElems];
@@ -791,7 +790,6 @@ template <int N, bool FULL, int M>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(N <= 4 ? 2 : 1, N <= 4 ? 2 : 1)))
 gmres_schur_elem_kernel(const HeviParams h, const GmresArgs g, const int ngrp)
 {
-    if (g.gate && *g.gate == 0) return;
     using Op = SchurOp<N, FULL>;
     constexpr int S = N;
     __shared__ double sc[Op::NC][kColElems];
@@ -998,7 +996,6 @@ template <int N, bool FULL, int M, int VR>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 gmres_half_kernel(const HeviParams h, const GmresArgs g, const int ngrp)
 {
-    if (g.gate && *g.gate == 0) return;
     using Op = HalfOp<N, FULL>;
     constexpr int H = Op::H, S = Op::S, XT = Op::XT, ML = M > VR ? M - VR : 0;
     __shared__ double sc[Op::NC][32];

@@ -122,7 +122,6 @@ __device__ void column_apply(const HeviParams &h, double alpha, const double *x,
 
 __global__ void __launch_bounds__(64) gmres_column_kernel(HeviParams h, GmresArgs g)
 {
-    if (g.gate && *g.gate == 0) return;
     extern __shared__ double smem[];
     const int nz = h.nz, NU = 3 * nz, m = g.restart, lane = threadIdx.x;
     const int NC = 2 * h.N + 1;
@@ -393,7 +392,6 @@ __device__ __forceinline__ void wave_sync()
 template <int M, int S>
 __global__ void __launch_bounds__(64) gmres_reg_kernel(HeviParams h, GmresArgs g)
 {
-    if (g.gate && *g.gate == 0) return;
     extern __shared__ double smem[];
     const int nz = h.nz, NU = 3 * nz, N = h.N, NC = 2 * N + 1, lane = threadIdx.x;
     const int NP = nz + 2 * N;            // padded length of the L_v intermediates
@@ -696,7 +694,6 @@ __global__ void __launch_bounds__(64) gmres_reg_kernel(HeviParams h, GmresArgs g
 template <int M, int S>
 __global__ void __launch_bounds__(64) gmres_schur_kernel(HeviParams h, GmresArgs g)
 {
-    if (g.gate && *g.gate == 0) return;
     extern __shared__ double smem[];
     const int nz = h.nz, N = h.N, NC = 2 * N + 1, lane = threadIdx.x;
     const int NP = nz + 2 * N;

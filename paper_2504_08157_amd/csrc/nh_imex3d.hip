@@ -14,11 +14,12 @@
 // solved by restarted GMRES with classical Gram-Schmidt (a second pass when
 // the kept norm falls below 1e-2 of the vector's), its dot products reduced
 // in a fixed order and its small Hessenberg problem solved on the device;
-// optionally right-preconditioned by the column systems of the 1D split
-// (flexible GMRES, since those are solved iteratively).
+// optionally right-preconditioned by the column systems of the 1D split,
+// solved directly (the preconditioned vectors are kept, as flexible GMRES does).
 #include "nh_internal.h"
 
 #include <cmath>
+#include <utility>
 #include <vector>
 
 namespace nh {
@@ -508,17 +509,277 @@ struct Kry {
 
 }  // namespace
 
-// z = (I - alpha L_v)^-1 v column by column (column GMRES(10) to rtol 1e-6;
-// the Schur form where the column is short enough); u, v rows are copied
-static hipError_t column_precond(const L3Params &h, double alpha, const double *v, double *z, const int *gate,
-                                 hipStream_t s)
+// ---- column preconditioner z = (I - alpha L_v)^-1 v, solved directly.  The
+// reference state depends on z alone, so every column has the same matrix, and
+// with rho' and theta' eliminated
+//   M w = b_w - alpha (1/rho0) (D p_b + g b_rho),   p_b = gamma p0 (b_rho/rho0 + b_theta/theta0),
+//   rho' = b_rho - alpha D (rho0 w),   theta' = b_theta - alpha theta0' w
+// (D: the DSS'd vertical derivative; identity rows of M and unchanged w at the
+// walls).  pc_setup_kernel forms M from three stencil rows, inverts it (n_z <= 130:
+// in the LDS of one workgroup) and stores M^-1 and D as operands of
+// v_mfma_f64_16x16x4_f64, once per solve.  pc_apply_kernel then is three small
+// products per column, on the matrix cores: a wave holds 16 columns, column
+// lane % 16, and of block s of four levels the level 4 s + lane / 16.  That is the
+// B operand of k step s (k = lane / 16) and also the layout of the result (row
+// 4 i + lane / 16 in register i), so a product feeds the next without a shuffle
+// or LDS.
+// Bound: the pass over memory, 5 fields read and 5 written (41 us for the 65536
+// columns of 41 levels of a 64 x 64 x 10, N = 4 mesh at the 5.15 TB/s of a copy;
+// 7 us of products): 48 us, where the column GMRES(10) to 1e-6 took 198.
+constexpr int kPcMaxTiles = 9;   // 16-level tiles: n_z <= 130 (and 144)
+
+__host__ __device__ constexpr int pc_halo(int N) { return (N + 3) / 4; }   // blocks of four levels beside a tile's own
+__host__ __device__ constexpr int pc_band(int HB) { return 4 + 2 * HB; }
+
+// packed operands: [T][4 NT][64] of M^-1, then [T][pc_band][64] of D
+static size_t pc_doubles(int nz, int N)
 {
-    GmresArgs g{};
-    g.b = v; g.x0 = nullptr; g.x = z; g.alpha = alpha; g.rtol = 1e-6;
-    g.restart = kGmresRegM; g.max_restarts = 10; g.iters = nullptr;
-    g.schur = h.nz - 2 <= 64 * kGmresSchurSlots ? 1 : 0;
-    g.gate = gate;
-    return launch_gmres(h.hv, g, s);
+    const size_t NT = (nz + 15) / 16;
+    return 64 * NT * (4 * NT + pc_band(pc_halo(N)));
+}
+
+size_t g3_precond_bytes(int nz, int N) { return nz <= 16 * kPcMaxTiles ? sizeof(double) * pc_doubles(nz, N) : 0; }
+
+constexpr int kPcThreads = 512;
+
+// M from the level table and the stencil rows (staged in LDS), then Gauss-Jordan
+// with partial pivoting in place: each step a pivot search by wave 0, then rank
+// one over the whole matrix; the column order is undone when the operands are
+// written.  83 us for 41 levels, once per step (its solves
+// share alpha).
+__global__ void __launch_bounds__(kPcThreads) pc_setup_kernel(HeviParams h, double alpha, double *__restrict__ pack)
+{
+    extern __shared__ double lds[];
+    const int n = h.nz, N = h.N, NC = 2 * N + 1, ld = n + 1, t = threadIdx.x;
+    const int lane = t % 64, wave = t / 64;
+    double *A = lds, *rowk = A + n * ld, *colk = rowk + n, *L0 = colk + n, *Lp = L0 + n, *L3 = Lp + n, *L7 = L3 + n,
+           *L8 = L7 + n, *G = L8 + n, *piv_l = G + n * NC;
+    int *pv = (int *)(piv_l + 1), *perm = pv + n;
+    for (int k = t; k < n; k += kPcThreads) {
+        const double *L = h.lev + (long)k * kLevW;
+        L0[k] = L[0];
+        Lp[k] = h.gamma * L[2];
+        L3[k] = L[3];
+        L7[k] = L[7];
+        L8[k] = L[8];
+    }
+    for (int e = t; e < n * NC; e += kPcThreads) G[e] = h.gz[e];
+    __syncthreads();
+    for (int i = wave; i < n; i += kPcThreads / 64)
+        for (int j = lane; j < n; j += 64) {
+            double m = i == j ? 1.0 : 0.0;
+            if (i > 0 && i < n - 1) {
+                // column j: rho'_k = -alpha D_kj rho0_j, theta'_j = -alpha theta0'_j
+                const double cj = -alpha * L0[j];
+                auto D = [&](int r, int c) { return c - r >= -N && c - r <= N ? G[r * NC + c - r + N] : 0.0; };
+                double dp = 0.0;
+                for (int k = i > N ? i - N : 0; k <= i + N && k < n; ++k) {
+                    double pk = cj * D(k, j) * L7[k];
+                    if (k == j) pk -= alpha * L3[j] * L8[k];
+                    dp += D(i, k) * Lp[k] * pk;
+                }
+                m += alpha * L7[i] * (dp + h.g * cj * D(i, j));
+            }
+            A[i * ld + j] = m;
+        }
+    __syncthreads();
+    for (int k = 0; k < n; ++k) {
+        if (t < 64) {
+            double best = -1.0;
+            int bi = k;
+            for (int i = k + t; i < n; i += 64) {
+                const double v = fabs(A[i * ld + k]);
+                if (v > best) {
+                    best = v;
+                    bi = i;
+                }
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                const double v = __shfl_xor(best, o);
+                const int vi = __shfl_xor(bi, o);
+                if (v > best || (v == best && vi < bi)) {
+                    best = v;
+                    bi = vi;
+                }
+            }
+            if (t == 0) {
+                pv[k] = bi;
+                *piv_l = 1.0 / A[bi * ld + k];
+            }
+        }
+        __syncthreads();
+        const int p = pv[k];
+        const double ip = *piv_l;
+        // the pivot row out, row k in its place (only row p is written), and column k
+        for (int j = t; j < n; j += kPcThreads) {
+            colk[j] = A[(j == p ? k : j) * ld + k];
+            const double r = A[p * ld + j];
+            A[p * ld + j] = A[k * ld + j];
+            rowk[j] = j == k ? ip : r * ip;
+        }
+        __syncthreads();
+        for (int j = lane; j < n; j += 64) {
+            const double r = rowk[j];
+            for (int i = wave; i < n; i += kPcThreads / 64)
+                A[i * ld + j] = i == k ? r : (j == k ? 0.0 : A[i * ld + j]) - colk[i] * r;
+        }
+        __syncthreads();
+    }
+    for (int j = t; j < n; j += kPcThreads) {   // the exchanges of columns, last first
+        int c = j;
+        for (int k = 0; k < n; ++k) c = c == k ? pv[k] : c == pv[k] ? k : c;
+        perm[j] = c;
+    }
+    __syncthreads();
+    const int NT = (n + 15) / 16, S = 4 * NT, HB = (N + 3) / 4, NB = pc_band(HB);
+    for (int e = t; e < NT * S * 64; e += kPcThreads) {
+        const int l = e % 64, s = e / 64 % S, T = e / (64 * S);
+        const int i = 16 * T + l % 16, k = 4 * s + l / 16;
+        pack[e] = i < n && k < n ? A[i * ld + perm[k]] : 0.0;
+    }
+    double *pd = pack + (long)NT * S * 64;
+    for (int e = t; e < NT * NB * 64; e += kPcThreads) {
+        const int l = e % 64, b = e / 64 % NB, T = e / (64 * NB);
+        const int i = 16 * T + l % 16, k = 4 * (4 * T - HB + b) + l / 16;
+        pd[e] = i < n && k >= 0 && k < n && k - i >= -N && k - i <= N ? G[i * NC + k - i + N] : 0.0;
+    }
+}
+
+template <int NT, int HB>
+__global__ void __launch_bounds__(256) pc_apply_kernel(HeviParams h, double alpha, const double *__restrict__ v,
+                                                       double *__restrict__ z, const double *__restrict__ pack,
+                                                       const double *__restrict__ lev, const int *gate)
+{
+    if (gate && *gate == 0) return;
+    typedef double double4v __attribute__((ext_vector_type(4)));
+    constexpr int S = 4 * NT, NB = pc_band(HB);
+    const int lane = threadIdx.x % 64, q = lane / 16;
+    const long nxy = (long)h.nx * h.ny, U = nxy * h.nz;
+    const long c0 = (blockIdx.x * 4L + threadIdx.x / 64) * 16;
+    if (c0 >= nxy) return;
+    const long c = c0 + lane % 16;
+    const bool own = c < nxy;
+    const double *x = v + (own ? c : nxy - 1);
+    double *y = z + c;
+    const int nz = h.nz;
+    // u and v with the other loads where registers allow, else at the end
+    constexpr bool kUvFirst = NT <= 4;
+    double br[S], bw[S], bt[S], bu[kUvFirst ? S : 1], bv[kUvFirst ? S : 1];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int k = 4 * s + q;
+        const long o = (long)(k < nz ? k : nz - 1) * nxy;
+        br[s] = x[o];
+        if constexpr (kUvFirst) {
+            bu[s] = x[U + o];
+            bv[s] = x[2 * U + o];
+        }
+        bw[s] = x[3 * U + o];
+        bt[s] = x[4 * U + o];
+    }
+    const double *pm = pack + lane, *pd = pack + (long)NT * S * 64 + lane;
+    // acc = D u over the levels of tile T
+    auto deriv = [&](int T, const double (&u)[S]) __attribute__((always_inline)) {
+        double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int s = 4 * T - HB + b;
+            if (s >= 0 && s < S) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pd[(T * NB + b) * 64], u[s], acc, 0, 0, 0);
+        }
+        return acc;
+    };
+    double u[S];   // p_b, then rho0 w
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int k = 4 * s + q;
+        const bool in = k < nz;
+        const double *L = lev + (long)(in ? k : nz - 1) * kLevW;
+        u[s] = in ? h.gamma * L[2] * (br[s] * L[7] + bt[s] * L[8]) : 0.0;
+        if constexpr (kUvFirst)
+            if (own && in) {
+                const long o = (long)k * nxy;
+                y[U + o] = bu[s];
+                y[2 * U + o] = bv[s];
+            }
+    }
+    double w[S];   // right-hand sides
+#pragma unroll
+    for (int T = 0; T < NT; ++T) {
+        const double4v acc = deriv(T, u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int s = 4 * T + i, k = 4 * s + q;
+            const double L7 = lev[(long)(k < nz ? k : nz - 1) * kLevW + 7];
+            const double r = k > 0 && k < nz - 1 ? bw[s] - alpha * L7 * (acc[i] + h.g * br[s]) : bw[s];
+            w[s] = k < nz ? r : 0.0;
+        }
+    }
+#pragma unroll
+    for (int T = 0; T < NT; ++T) {
+        double4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pm[(T * S + s) * 64], w[s], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bw[4 * T + i] = acc[i];
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int k = 4 * s + q;
+        const bool in = k < nz;
+        const double *L = lev + (long)(in ? k : nz - 1) * kLevW;
+        u[s] = in ? L[0] * bw[s] : 0.0;
+        if (own && in) {
+            const long o = (long)k * nxy;
+            y[3 * U + o] = bw[s];
+            y[4 * U + o] = bt[s] - alpha * L[3] * bw[s];
+        }
+    }
+#pragma unroll
+    for (int T = 0; T < NT; ++T) {
+        const double4v acc = deriv(T, u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int s = 4 * T + i, k = 4 * s + q;
+            if (own && k < nz) y[(long)k * nxy] = br[s] - alpha * acc[i];
+        }
+    }
+    if constexpr (!kUvFirst) {
+#pragma unroll 8
+        for (int s = 0; s < S; ++s) {
+            const int k = 4 * s + q;
+            if (own && k < nz) {
+                const long o = (long)k * nxy;
+                y[U + o] = x[U + o];
+                y[2 * U + o] = x[2 * U + o];
+            }
+        }
+    }
+}
+
+static hipError_t launch_pc_setup(const L3Params &h, double alpha, double *pack, hipStream_t s)
+{
+    const size_t n = h.nz, lds = sizeof(double) * (n * (n + 1) + 7 * n + n * (2 * h.N + 1) + 1) + sizeof(int) * 2 * n;
+    hipLaunchKernelGGL(pc_setup_kernel, dim3(1), dim3(kPcThreads), lds, s, h.hv, alpha, pack);
+    return hipGetLastError();
+}
+
+template <int NT>
+static hipError_t launch_pc_apply(int nt, const L3Params &h, double alpha, const double *v, double *z,
+                                  const double *pack, const int *gate, hipStream_t s)
+{
+    if constexpr (NT > kPcMaxTiles) {
+        return hipErrorInvalidValue;
+    } else {
+        if (nt != NT) return launch_pc_apply<NT + 1>(nt, h, alpha, v, z, pack, gate, s);
+        const dim3 grid((unsigned)(((long)h.nx * h.ny + 63) / 64)), blk(256);
+        if (pc_halo(h.N) == 1)
+            hipLaunchKernelGGL((pc_apply_kernel<NT, 1>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate);
+        else
+            hipLaunchKernelGGL((pc_apply_kernel<NT, 2>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate);
+        return hipGetLastError();
+    }
 }
 
 // The host queues one Arnoldi step while the previous one runs: before it
@@ -527,7 +788,8 @@ static hipError_t column_precond(const L3Params &h, double alpha, const double *
 // queued past the end of the process, and that one does nothing.  One
 // stream synchronisation per solve reads the result.
 hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const double *b, const double *x0, double *x,
-                   int m, int max_restarts, double rtol, bool precond, hipStream_t s, int *iters, double *relres)
+                   int m, int max_restarts, double rtol, bool precond, bool pc_ready, hipStream_t s, int *iters,
+                   double *relres)
 {
     const long n = (long)kNF * h.nx * h.ny * h.nz;
     Kry k{w, s, n};
@@ -536,6 +798,7 @@ hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const doubl
     double *V = w.V;   // (m + 1) vectors of n
     *iters = 0;
     *relres = 0.0;
+    if (precond && !pc_ready && (e = launch_pc_setup(h, alpha, w.pc, s)) != hipSuccess) return e;
     // ||b||, x = x0 (or b); x = 0 when b = 0
     k.dots(V, 0, b, nullptr);
     hipLaunchKernelGGL(g3_begin_kernel, dim3(1), dim3(kKryCtl), 0, s, st, (const double *)w.part, w.status_dev);
@@ -566,7 +829,7 @@ hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const doubl
             const double *zj = vj;
             if (precond) {
                 double *zz = w.Z + (long)j * n;
-                if ((e = column_precond(h, alpha, vj, zz, &st->go, s)) != hipSuccess) return e;
+                if ((e = launch_pc_apply<1>((h.nz + 15) / 16, h, alpha, vj, zz, w.pc, &st->go, s)) != hipSuccess) return e;
                 zj = zz;
             }
             if ((e = launch_l3(h, zj, vn, 1.0, -alpha, s, &st->go)) != hipSuccess) return e;

@@ -154,7 +154,6 @@ struct GmresArgs {
     int *iters;          // [n_x n_y] Arnoldi steps per column (negative: not converged), or null
     int schur;           // 1: solve the Schur complement in w (restart kGmresRegM only)
     int pick;            // with x0: per column, start from x0 or from b, whichever has the smaller residual
-    const int *gate;     // device flag: the launch does nothing while it is 0 (null: always runs)
 };
 
 constexpr int kMaxComb = 6;
@@ -225,6 +224,7 @@ struct G3Work {
     double *Z;      // restart preconditioned vectors (flexible GMRES)
     double *t;      // one 5U vector
     double *part;   // [35][1024] block partial sums, quantity-major
+    double *pc;     // operands of the column preconditioner (g3_precond_bytes)
     G3State *state;                 // device
     G3Status *status_dev;           // host-mapped status, device address
     const volatile G3Status *status;  // the same, host address
@@ -234,11 +234,14 @@ struct G3Work {
 // flag) nothing is done while it is 0
 hipError_t launch_l3(const L3Params &h, const double *x, double *out, double a, double c, hipStream_t s,
                      const int *gate = nullptr);
+size_t g3_precond_bytes(int nz, int N);
 // (I - alpha L) x = b by restarted GMRES(m); iters = Arnoldi steps, relres =
 // final ||b - A x|| / ||b||
-// precond: right-precondition with the column systems (I - alpha L_v)
+// precond: right-precondition with the column systems (I - alpha L_v); pc_ready: w.pc
+// holds their operands for this alpha already
 hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const double *b, const double *x0, double *x,
-                   int m, int max_restarts, double rtol, bool precond, hipStream_t s, int *iters, double *relres);
+                   int m, int max_restarts, double rtol, bool precond, bool pc_ready, hipStream_t s, int *iters,
+                   double *relres);
 
 // ---- RI-velocity diagnostic
 constexpr int kRiMaxStrips = 4096;

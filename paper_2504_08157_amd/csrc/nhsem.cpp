@@ -1233,6 +1233,7 @@ static size_t g3_bytes(const nh_ctx *c, int restart, bool step, G3Work *w, doubl
     g.t = (double *)take(nv);
     g.part = (double *)take(sizeof(double) * 1024 * 35);
     g.state = (G3State *)take(sizeof(G3State));
+    g.pc = (double *)take(g3_precond_bytes(c->n[2], c->N));
     if (step)
         for (int i = 0; i < 8; ++i) {
             double *a = (double *)take(nv);
@@ -1340,7 +1341,7 @@ nh_status nh_global_solve(nh_ctx *c, double alpha, const double *dev_b, const do
     int it = 0;
     double rr = 0.0;
     HIPCHK(c, gmres3d(l3_params(c), w, alpha, dev_b, dev_x0, dev_x, opts->restart, opts->max_restarts, opts->rtol,
-                      opts->precondition != 0, c->stream, &it, &rr));
+                      opts->precondition != 0, false, c->stream, &it, &rr));
     g3_count(stats, it, rr, opts->rtol);
     if (!(rr <= opts->rtol)) return fail(c, NH_ENOCONV, "global GMRES: relative residual %.3e > %.3e", rr, opts->rtol);
     return NH_OK;
@@ -1382,7 +1383,7 @@ nh_status nh_imex3d_step(nh_ctx *c, double t, double dt, const nh_gmres_opts *op
             int it = 0;
             double rr = 0.0;
             HIPCHK(c, gmres3d(h, w, dt * ark.At[i][i], R, R, Q[i], opts->restart, opts->max_restarts, opts->rtol,
-                              opts->precondition != 0, c->stream, &it, &rr));
+                              opts->precondition != 0, i == 2 && ark.At[2][2] == ark.At[1][1], c->stream, &it, &rr));
             g3_count(stats, it, rr, opts->rtol);
             missed = missed || !(rr <= opts->rtol);
         }
