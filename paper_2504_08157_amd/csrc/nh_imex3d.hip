@@ -27,17 +27,21 @@ namespace nh {
 // out[f] = a x[f] + c (L x)[f] at every node, all of L in one walk (out may
 // not alias x).  Walls: u rows zero at x walls, v rows at y walls, w rows at
 // the bottom and top.  A workgroup of 64 x 8 lattice columns walks a chunk
-// of kL3KZ levels.  Per level it stages the planes of u, v and p'_L of its
+// of kz levels.  Per level it stages the planes of u, v and p'_L of its
 // tile plus an N-wide x/y halo in LDS (two buffers, one barrier per level)
-// for the x and y taps; the vertical part (L_v) comes from a (2N+1)-level
-// window of rho0 w and p'_L of the thread's own column in registers, filled
-// with the N levels below the chunk and the N levels above each level as
-// the walk goes (taps outside the column see zero inputs), as in the
-// column-walking L_v kernel.  All loads of a level, the window's lead level
-// included, are issued two levels ahead into register slots indexed at
-// compile time.  Chunks of levels give enough workgroups on meshes of few
-// columns.
-constexpr int kL3TX = 64, kL3TY = 8, kL3KZ = 16, kL3P = 2;
+// for the x and y taps; each thread stages its own node, which it needs
+// itself, and up to two of the halo.  The vertical part (L_v) comes from a
+// (2N+1)-level window of rho0 w and p'_L of the thread's own column in
+// registers, filled with the N levels below the chunk and the N levels above
+// each level as the walk goes (taps outside the column see zero inputs), as in
+// the column-walking L_v kernel.  The loads of a level, the window's lead level
+// included, are issued one level ahead.  Bound: the LDS taps and the latency of a
+// level (2 us with one workgroup on a CU), not memory: what counts is that two
+// workgroups share a CU, so registers are held to 128 for N <= 4 (the y stencil
+// row, one per wave, is in scalar registers; node offsets are 32 bits on uniform
+// level bases), and that the chunks spread evenly over the CUs (l3_levels).
+// 256 x 256 x 41 nodes, N = 4: 55 us (85 before), 41 at the rate of a copy.
+constexpr int kL3TX = 64, kL3TY = 8, kL3P = 1;
 
 __device__ __forceinline__ int l3_xcd_block(int b, int n)
 {
@@ -57,14 +61,15 @@ __device__ __forceinline__ void l3_unrolled(F &&f)
 // (lev and gz are h.lev and h.hv.gz passed again as restrict pointers so
 // that their per-level values are read with scalar loads)
 template <int N>
-__global__ void __launch_bounds__(kL3TX * kL3TY) l3_tile_kernel(L3Params h, const double *__restrict__ x,
+__global__ void __launch_bounds__(kL3TX * kL3TY, N <= 4 ? 4 : 2) l3_tile_kernel(L3Params h, const double *__restrict__ x,
                                                                 double *out, double a, double c,
                                                                 const double *__restrict__ lev,
-                                                                const double *__restrict__ gz, const int *gate)
+                                                                const double *__restrict__ gz, int kz,
+                                                                const int *gate)
 {
     if (gate && *gate == 0) return;
     constexpr int NC = 2 * N + 1, PX = kL3TX + 2 * N, PY = kL3TY + 2 * N, PS = PX * PY;
-    constexpr int NT = kL3TX * kL3TY, NS = (PS + NT - 1) / NT, P = kL3P;
+    constexpr int NT = kL3TX * kL3TY, NH = (PS - NT + NT - 1) / NT, P = kL3P;   // NH: halo nodes per thread
     __shared__ double tile[2][3][PS];   // u, v, p'_L
     const long nxy = (long)h.nx * h.ny;
     const int nz = h.nz;
@@ -72,26 +77,31 @@ __global__ void __launch_bounds__(kL3TX * kL3TY) l3_tile_kernel(L3Params h, cons
     const int ntx = (h.nx + kL3TX - 1) / kL3TX, nty = (h.ny + kL3TY - 1) / kL3TY;
     const int t = l3_xcd_block(blockIdx.x, gridDim.x);
     const int tt = t % (ntx * nty), kc = t / (ntx * nty);
-    const int kb = kc * kL3KZ, ke = kb + kL3KZ < nz ? kb + kL3KZ : nz;
-    const int tx = threadIdx.x % kL3TX, ty = threadIdx.x / kL3TX;
+    const int kb = kc * kz, ke = kb + kz < nz ? kb + kz : nz;
+    const int tx = threadIdx.x % kL3TX, ty = __builtin_amdgcn_readfirstlane(threadIdx.x / kL3TX);
     const int x0 = (tt % ntx) * kL3TX, y0 = (tt / ntx) * kL3TY;
     const int ix = x0 + tx, iy = y0 + ty;
     const bool own = ix < h.nx && iy < h.ny;
-    const long col = own ? ix + (long)iy * h.nx : 0;
+    const unsigned col = own ? ix + iy * h.nx : 0;
     const double gamma = h.gamma, grav = h.hv.g;
     double cx[NC], cy[NC];
 #pragma unroll
     for (int o = 0; o < NC; ++o) {
-        cx[o] = own ? h.gx[(long)ix * NC + o] : 0.0;
-        cy[o] = own ? h.gy[(long)iy * NC + o] : 0.0;
+        cx[o] = h.gx[(long)(ix < h.nx ? ix : 0) * NC + o];
+        cy[o] = h.gy[(long)(iy < h.ny ? iy : 0) * NC + o];   // one row of the lattice per wave
     }
-    long sc[NS];
-    bool sv[NS];
+    // the halo nodes: N rows below and above the tile, then N columns on each side
+    unsigned sc[NH];
+    int si[NH];   // place in the tile, -1: none
+    bool sv[NH];
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        const int s = threadIdx.x + i * NT;
-        int jx = x0 - N + s % PX, jy = y0 - N + s / PX;
-        bool ok = s < PS;
+    for (int i = 0; i < NH; ++i) {
+        const int e = threadIdx.x + i * NT, f = e - 2 * N * PX;
+        const int r = e / PX, g = f % (2 * N);
+        const int px = f < 0 ? e % PX : g < N ? g : g + kL3TX, py = f < 0 ? (r < N ? r : r + kL3TY) : N + f / (2 * N);
+        int jx = x0 - N + px, jy = y0 - N + py;
+        bool ok = e < PS - NT;
+        si[i] = ok ? py * PX + px : -1;
         if (jx < 0 || jx >= h.nx) {
             ok = ok && h.perx;
             jx = ((jx % h.nx) + h.nx) % h.nx;
@@ -101,8 +111,12 @@ __global__ void __launch_bounds__(kL3TX * kL3TY) l3_tile_kernel(L3Params h, cons
             jy = ((jy % h.ny) + h.ny) % h.ny;
         }
         sv[i] = ok;
-        sc[i] = ok ? jx + (long)jy * h.nx : 0;
+        sc[i] = ok ? jx + jy * h.nx : 0;
     }
+    // the thread's own node: beyond the lattice (a ragged tile) it is a halo node of its neighbours
+    const bool inx = ix < h.nx || h.perx, iny = iy < h.ny || h.pery, okc = inx && iny;
+    const unsigned cs = okc ? ix % h.nx + (iy % h.ny) * h.nx : 0;
+    const int jo = (ty + N) * PX + tx + N;
     auto level = [&](int k) -> long { return (long)(k < ke ? k : ke - 1) * nxy; };
     // rho0 w and p'_L of the own column at level kk (zero outside the column)
     auto vert = [&](int kk, double r, double w, double th, double &va, double &vb) {
@@ -117,48 +131,50 @@ __global__ void __launch_bounds__(kL3TX * kL3TY) l3_tile_kernel(L3Params h, cons
     for (int o = 0; o < 2 * N; ++o) {
         const int kk = kb - N + o;
         const long L = (long)(kk < 0 ? 0 : kk < nz ? kk : nz - 1) * nxy;
-        vert(kk, x[col + L], x[3 * U + col + L], x[4 * U + col + L], ta[o], tb[o]);
+        vert(kk, (x + L)[col], (x + 3 * U + L)[col], (x + 4 * U + L)[col], ta[o], tb[o]);
     }
-    // slot contents: staged rho', u, v, theta' of NS nodes; own rho', w,
-    // theta' of x at the level and at the window's lead level (level + N)
-    double sr[P][NS], su[P][NS], sv2[P][NS], st[P][NS], ox[P][3], oz[P][3];
+    // slot contents: rho', u, v, theta' of the halo nodes; all fields of the
+    // thread's node (rho', u, v, w, theta'); rho', w, theta' of its column at the
+    // window's lead level (level + N)
+    double sr[P][NH], su[P][NH], sv2[P][NH], st[P][NH], ox[P][5], oz[P][3];
     auto load = [&](int p, int k) {
-        const long L = level(k);
+        const double *xl = x + level(k);
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            sr[p][i] = x[sc[i] + L];
-            su[p][i] = x[U + sc[i] + L];
-            sv2[p][i] = x[2 * U + sc[i] + L];
-            st[p][i] = x[4 * U + sc[i] + L];
+        for (int i = 0; i < NH; ++i) {
+            sr[p][i] = xl[sc[i]];
+            su[p][i] = (xl + U)[sc[i]];
+            sv2[p][i] = (xl + 2 * U)[sc[i]];
+            st[p][i] = (xl + 4 * U)[sc[i]];
         }
-        ox[p][0] = x[col + L];
-        ox[p][1] = x[3 * U + col + L];
-        ox[p][2] = x[4 * U + col + L];
+#pragma unroll
+        for (int f = 0; f < 5; ++f) ox[p][f] = (xl + f * U)[cs];
         const int kz = k + N;
-        const long Z = (long)(kz < nz ? kz : nz - 1) * nxy;
-        oz[p][0] = x[col + Z];
-        oz[p][1] = x[3 * U + col + Z];
-        oz[p][2] = x[4 * U + col + Z];
+        const double *xz = x + (long)(kz < nz ? kz : nz - 1) * nxy;
+        oz[p][0] = xz[col];
+        oz[p][1] = (xz + 3 * U)[col];
+        oz[p][2] = (xz + 4 * U)[col];
     };
     l3_unrolled<0, P>([&](auto J) { load(decltype(J)::value, kb + decltype(J)::value); });
     for (int k0 = kb; k0 < ke; k0 += P) {
         l3_unrolled<0, P>([&](auto J) {
             constexpr int j = decltype(J)::value;
             const int k = k0 + j;
-            const double *Lv = lev + level(k) / nxy * kLevW;
+            const double *Lv = lev + (long)(k < ke ? k : ke - 1) * kLevW;
             const double rho0 = Lv[0], p0 = Lv[2], dth0 = Lv[3], tau = Lv[4], irho0 = Lv[7], ith0 = Lv[8];
             const double gp = gamma * p0;
             double(*T)[PS] = tile[(k - kb) & 1];
 #pragma unroll
-            for (int i = 0; i < NS; ++i) {
-                const int sidx = threadIdx.x + i * NT;
-                if (sidx < PS) {
-                    T[0][sidx] = sv[i] ? su[j][i] : 0.0;
-                    T[1][sidx] = sv[i] ? sv2[j][i] : 0.0;
-                    T[2][sidx] = sv[i] ? gp * (sr[j][i] * irho0 + st[j][i] * ith0) : 0.0;
+            for (int i = 0; i < NH; ++i) {
+                if (si[i] >= 0) {
+                    T[0][si[i]] = sv[i] ? su[j][i] : 0.0;
+                    T[1][si[i]] = sv[i] ? sv2[j][i] : 0.0;
+                    T[2][si[i]] = sv[i] ? gp * (sr[j][i] * irho0 + st[j][i] * ith0) : 0.0;
                 }
             }
-            const double xr = ox[j][0], xw = ox[j][1], xt = ox[j][2];
+            const double xr = ox[j][0], xu = ox[j][1], xv = ox[j][2], xw = ox[j][3], xt = ox[j][4];
+            T[0][jo] = okc ? xu : 0.0;
+            T[1][jo] = okc ? xv : 0.0;
+            T[2][jo] = okc ? gp * (xr * irho0 + xt * ith0) : 0.0;
             vert(k + N, oz[j][0], oz[j][1], oz[j][2], ta[2 * N], tb[2 * N]);
             load(j, k + P);
             // vertical part at level k
@@ -184,8 +200,6 @@ __global__ void __launch_bounds__(kL3TX * kL3TY) l3_tile_kernel(L3Params h, cons
                 dvy += cy[o] * T[1][jy];
                 dpy += cy[o] * T[2][jy];
             }
-            const int jo = (ty + N) * PX + tx + N;
-            const double xu = T[0][jo], xv = T[1][jo];
             double Lr = -d_rw - rho0 * (dux + dvy);
             double Lu = -irho0 * dpx, Lvv = -irho0 * dpy;
             double Lw = -d_pl * irho0 - grav * xr * irho0 - tau * xw;
@@ -194,29 +208,51 @@ __global__ void __launch_bounds__(kL3TX * kL3TY) l3_tile_kernel(L3Params h, cons
             if (!h.pery && (iy == 0 || iy == h.ny - 1)) Lvv = 0.0;
             if (k == 0 || k == nz - 1) Lw = 0.0;
             if (own && k < ke) {
-                const long I = col + (long)k * nxy;
-                out[I] = a * xr + c * Lr;
-                out[U + I] = a * xu + c * Lu;
-                out[2 * U + I] = a * xv + c * Lvv;
-                out[3 * U + I] = a * xw + c * Lw;
-                out[4 * U + I] = a * xt + c * Lt;
+                double *ol = out + (long)k * nxy;
+                ol[col] = a * xr + c * Lr;
+                (ol + U)[col] = a * xu + c * Lu;
+                (ol + 2 * U)[col] = a * xv + c * Lvv;
+                (ol + 3 * U)[col] = a * xw + c * Lw;
+                (ol + 4 * U)[col] = a * xt + c * Lt;
             }
         });
     }
+}
+
+// Levels per chunk: a CU that gets r workgroups takes about (r + 0.4) times the
+// levels of a chunk and 2.5 levels' worth of window fill and start (orders up to 4:
+// two workgroups on a CU at a time; above, one: r times).  Measured on 256 x 256
+// x 41 nodes, N = 4 (128 tiles), chunks of 41, 21, 16, 14, 11, 7, 5 levels: 96.3, 62.8, 65.5,
+// 59.3, 55.1, 57.3, 69.6 us; on 384 x 384 x 65 (288 tiles), 65, 33, 22, 16, 13, 8: 326, 263,
+// 248, 276, 240, 272 us; on 48 x 48 x 49 (6 tiles), 41, 16, 4: 85.8, 37.4, 14.3 us.  (Chunks
+// of 16 levels in slots of two levels, one workgroup to a CU: 84.7, 330 and 36.6 us.)
+static int l3_levels(int tiles, int nz, int N)
+{
+    double best = 1e300;
+    int kz = nz;
+    for (int c = 1; c <= nz; ++c) {
+        const int k = (nz + c - 1) / c, r = (tiles * ((nz + k - 1) / k) + 255) / 256;
+        const double t = (r + (N <= 4 ? 0.4 : 0.0)) * (k + 2.5);
+        if (t < best) {
+            best = t;
+            kz = k;
+        }
+    }
+    return kz;
 }
 
 hipError_t launch_l3(const L3Params &h, const double *x, double *out, double a, double c, hipStream_t s,
                      const int *gate)
 {
     const int ntx = (h.nx + kL3TX - 1) / kL3TX, nty = (h.ny + kL3TY - 1) / kL3TY;
-    const int nkc = (h.nz + kL3KZ - 1) / kL3KZ;
+    const int kz = l3_levels(ntx * nty, h.nz, h.N), nkc = (h.nz + kz - 1) / kz;
     const dim3 grid((unsigned)(ntx * nty * nkc)), blk(kL3TX * kL3TY);
     switch (h.N) {
-    case 2: hipLaunchKernelGGL(l3_tile_kernel<2>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, gate); break;
-    case 3: hipLaunchKernelGGL(l3_tile_kernel<3>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, gate); break;
-    case 4: hipLaunchKernelGGL(l3_tile_kernel<4>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, gate); break;
-    case 5: hipLaunchKernelGGL(l3_tile_kernel<5>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, gate); break;
-    case 6: hipLaunchKernelGGL(l3_tile_kernel<6>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, gate); break;
+    case 2: hipLaunchKernelGGL(l3_tile_kernel<2>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
+    case 3: hipLaunchKernelGGL(l3_tile_kernel<3>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
+    case 4: hipLaunchKernelGGL(l3_tile_kernel<4>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
+    case 5: hipLaunchKernelGGL(l3_tile_kernel<5>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
+    case 6: hipLaunchKernelGGL(l3_tile_kernel<6>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
