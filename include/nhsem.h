@@ -302,7 +302,7 @@ typedef struct {
     int64_t not_converged;    /* column solves that missed rtol */
 } nh_solve_stats;
 
-/* Device workspace the HEVI calls need (8 state-sized arrays + counters). */
+/* Device workspace the HEVI calls need (9 state-sized arrays + counters). */
 nh_status nh_hevi_workspace_bytes(const nh_ctx *ctx, size_t *bytes);
 
 /* Attach that workspace (borrowed, 256-byte aligned). */

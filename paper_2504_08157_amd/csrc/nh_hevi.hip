@@ -80,6 +80,106 @@ __global__ void axpy_multi_kernel(long n, const double *__restrict__ base, int n
     }
 }
 
+// The explicit sides of the two implicit ARK2 stages, L_v taken in the same walk:
+//   NS = 1: r = q1 + c0 s0 + d0 L_v q1
+//   NS = 2: r = q1 + c0 s0 + d0 L_v q1 + c1 s1 + d1 L_v q2,
+//           p = q1 + b0 s0 + b1 s1 (the known part of the step's result)
+// One thread per lattice column and run of kz levels, a (2N+1)-level window of
+// the stencil inputs per state, as in the column-walking L_v kernel.  Bound:
+// memory; 15 and 28 fields instead of the 28 and 38 of L_v into an array and an
+// elementwise combination, and the step's last combination (20 fields) becomes
+// the third stage's own.  384 x 384 x 65 nodes, N = 4: 244 and 472 us (4.7
+// TB/s); L_v and the three combinations took 2 x 115 + 3 x 343 us.
+template <int N, int NS>
+__global__ void __launch_bounds__(256) ark_rhs_kernel(HeviParams h, ArkRhs a, int kz)
+{
+    constexpr int NC = 2 * N + 1;
+    const long nxy = (long)h.nx * h.ny, U = nxy * h.nz;
+    const long col = blockIdx.x * 256L + threadIdx.x;
+    if (col >= nxy) return;
+    const int nz = h.nz, k0 = blockIdx.y * kz, k1 = k0 + kz < nz ? k0 + kz : nz;
+    const double *qq[2] = {a.q1 + col, NS == 2 ? a.q2 + col : nullptr};
+    // rho0 w and p'_L of levels k - N .. k + N; rho', w, theta' of k .. k + N
+    double ta[NS][NC], tb[NS][NC], rr[NS][N + 1], ww[NS][N + 1], th[NS][N + 1];
+    auto load = [&](const double *q, int kk, double &ma, double &mb, double &r, double &w, double &t)
+                    __attribute__((always_inline)) {
+        const bool in = kk >= 0 && kk < nz;
+        const int kc = kk < 0 ? 0 : kk < nz ? kk : nz - 1;
+        const double *L = h.lev + (long)kc * kLevW;
+        const long J = kc * nxy;
+        r = q[J];
+        w = q[3 * U + J];
+        t = q[4 * U + J];
+        ma = in ? L[0] * w : 0.0;
+        mb = in ? h.gamma * L[2] * (r * L[7] + t * L[8]) : 0.0;
+    };
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        double u0, u1, u2;
+#pragma unroll
+        for (int o = 0; o < N; ++o) load(qq[i], k0 - N + o, ta[i][o], tb[i][o], u0, u1, u2);
+#pragma unroll
+        for (int j = 0; j < N; ++j) load(qq[i], k0 + j, ta[i][N + j], tb[i][N + j], rr[i][j], ww[i][j], th[i][j]);
+    }
+    for (int k = k0; k < k1; ++k) {
+        const long I = (long)k * nxy;
+        double s0[5], s1[5];
+        const double u = qq[0][U + I], v = qq[0][2 * U + I];
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+            s0[f] = a.s0[f * U + col + I];
+            if constexpr (NS == 2) s1[f] = a.s1[f * U + col + I];
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            load(qq[i], k + N, ta[i][2 * N], tb[i][2 * N], rr[i][N], ww[i][N], th[i][N]);
+        const double *L = h.lev + (long)k * kLevW;
+        const double *G = h.gz + (long)k * NC;
+        const bool wall = k == 0 || k == nz - 1;
+        double l[NS][5];
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            double d_rw = 0.0, d_pl = 0.0;
+#pragma unroll
+            for (int o = 0; o < NC; ++o) {
+                d_rw += G[o] * ta[i][o];
+                d_pl += G[o] * tb[i][o];
+            }
+            l[i][0] = -d_rw;
+            l[i][1] = l[i][2] = 0.0;
+            l[i][3] = wall ? 0.0 : -d_pl * L[7] - h.g * rr[i][0] * L[7];
+            l[i][4] = -ww[i][0] * L[3];
+        }
+        const double q[5] = {rr[0][0], u, v, ww[0][0], th[0][0]};
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+            double r = q[f];
+            r += a.c0 * s0[f];
+            r += a.d0 * l[0][f];
+            if constexpr (NS == 2) {
+                r += a.c1 * s1[f];
+                r += a.d1 * l[1][f];
+                double p = q[f];
+                p += a.b0 * s0[f];
+                p += a.b1 * s1[f];
+                a.p[f * U + col + I] = p;
+            }
+            a.r[f * U + col + I] = r;
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+#pragma unroll
+            for (int o = 0; o < 2 * N; ++o) { ta[i][o] = ta[i][o + 1]; tb[i][o] = tb[i][o + 1]; }
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                rr[i][j] = rr[i][j + 1];
+                ww[i][j] = ww[i][j + 1];
+                th[i][j] = th[i][j + 1];
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------- GMRES
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -1045,6 +1145,28 @@ hipError_t launch_lv_resid(const HeviParams &h, double alpha, const double *b, c
                            hipStream_t s)
 {
     return launch_lv<true>(h, x3, y, s, false, alpha, b);
+}
+
+// Runs of levels: enough threads for four waves on every SIMD, no run shorter
+// than 8 levels (each reads 2N levels of the window beside its own).
+hipError_t launch_ark_rhs(const HeviParams &h, const ArkRhs &a, hipStream_t s)
+{
+    const long nxy = (long)h.nx * h.ny, wg = (nxy + 255) / 256;
+    int runs = (int)((1024 + wg - 1) / wg);
+    if (runs > (h.nz + 7) / 8) runs = (h.nz + 7) / 8;
+    const int kz = (h.nz + runs - 1) / runs;
+    const dim3 grid((unsigned)wg, (unsigned)((h.nz + kz - 1) / kz)), blk(256);
+    switch (h.N) {
+#define NH_ARK(NN)                                                                                   \
+    case NN:                                                                                         \
+        if (a.q2) hipLaunchKernelGGL((ark_rhs_kernel<NN, 2>), grid, blk, 0, s, h, a, kz);            \
+        else hipLaunchKernelGGL((ark_rhs_kernel<NN, 1>), grid, blk, 0, s, h, a, kz);                 \
+        break;
+        NH_ARK(1) NH_ARK(2) NH_ARK(3) NH_ARK(4) NH_ARK(5) NH_ARK(6)
+#undef NH_ARK
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb &lc, double *out,

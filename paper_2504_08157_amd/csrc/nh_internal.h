@@ -162,6 +162,15 @@ struct LinComb {
     double c[kMaxComb];
 };
 
+// r = q1 + c0 s0 + d0 L_v q1 [+ c1 s1 + d1 L_v q2] on [5][U]; with q2 also
+// p = q1 + b0 s0 + b1 s1
+struct ArkRhs {
+    const double *q1, *q2, *s0, *s1;
+    double c0, c1, d0, d1, b0, b1;
+    double *r, *p;
+};
+hipError_t launch_ark_rhs(const HeviParams &h, const ArkRhs &a, hipStream_t s);
+
 size_t gmres_lds_bytes(int nz, int N, int restart);
 // y = L_v x on [5][U]; with uv false the u and v rows of y are left untouched
 hipError_t launch_lv_apply(const HeviParams &h, const double *x, double *y, hipStream_t s, bool uv = true);

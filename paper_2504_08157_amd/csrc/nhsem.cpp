@@ -844,7 +844,7 @@ struct Ark2 {
     }
 };
 
-constexpr int kHeviArrays = 11;  // S1 S2 S3 L1 L2 Q2 Q3 R2 R3, L_v R and the MLP guess
+constexpr int kHeviArrays = 9;   // S1 S2 P Q2 Q3 R2 R3, L_v R and the MLP guess
 
 size_t hevi_bytes(const nh_ctx *c)
 {
@@ -1129,10 +1129,10 @@ nh_status nh_hevi_last_solves(nh_ctx *c, const double **R2, const double **X2, c
     if (st) return st;
     if (!c->hws) return fail(c, NH_EINVAL, "no HEVI workspace attached");
     static const Ark2 ark;
-    if (R2) *R2 = hevi_arr(c, 7);
-    if (X2) *X2 = hevi_arr(c, 5);
-    if (R3) *R3 = hevi_arr(c, 8);
-    if (X3) *X3 = hevi_arr(c, 6);
+    if (R2) *R2 = hevi_arr(c, 5);
+    if (X2) *X2 = hevi_arr(c, 3);
+    if (R3) *R3 = hevi_arr(c, 6);
+    if (X3) *X3 = hevi_arr(c, 4);
     if (alpha) *alpha = ark.At[1][1];
     return NH_OK;
 }
@@ -1172,38 +1172,38 @@ nh_status nh_hevi_step(nh_ctx *c, double t, double dt, const nh_gmres_opts *opts
     if (!isfinite(t) || !(dt > 0.0) || !isfinite(dt)) return fail(c, NH_EINVAL, "bad time step");
     if ((st = check_gmres_opts(c, opts))) return st;
     static const Ark2 ark;
-    const long n = kNF * (long)c->U;
-    double *Q1 = c->q[0];
-    double *S[3] = {hevi_arr(c, 0), hevi_arr(c, 1), hevi_arr(c, 2)};
-    double *Lv[2] = {hevi_arr(c, 3), hevi_arr(c, 4)};
-    double *Q[3] = {Q1, hevi_arr(c, 5), hevi_arr(c, 6)};
-    double *Rs[3] = {nullptr, hevi_arr(c, 7), hevi_arr(c, 8)};
+    double *Q[3] = {c->q[0], hevi_arr(c, 3), hevi_arr(c, 4)};
+    double *S[2] = {hevi_arr(c, 0), hevi_arr(c, 1)}, *P = hevi_arr(c, 2);
+    double *Rs[3] = {nullptr, hevi_arr(c, 5), hevi_arr(c, 6)};
     const size_t ncol = (size_t)c->n[0] * c->n[1];
     for (int i = 0; i < 3; ++i) {
         if (i > 0) {
-            // R = q^n + dt sum_{j<i} [A_ij S_j + (At_ij - A_ij) L_j]
-            LinComb lc{};
-            int ns = 0;
-            for (int j = 0; j < i; ++j) {
-                lc.src[ns] = S[j]; lc.c[ns++] = dt * ark.A[i][j];
-                lc.src[ns] = Lv[j]; lc.c[ns++] = dt * (ark.At[i][j] - ark.A[i][j]);
-            }
+            // R = q^n + dt sum_{j<i} [A_ij S_j + (At_ij - A_ij) L_v Q_j]
+            ArkRhs a{};
             double *R = Rs[i];
-            HIPCHK(c, launch_axpy_multi(n, Q1, ns, lc, R, c->stream));
+            a.q1 = Q[0]; a.s0 = S[0]; a.r = R;
+            a.c0 = dt * ark.A[i][0];
+            a.d0 = dt * (ark.At[i][0] - ark.A[i][0]);
+            if (i == 2) {
+                a.q2 = Q[1]; a.s1 = S[1];
+                a.c1 = dt * ark.A[i][1];
+                a.d1 = dt * (ark.At[i][1] - ark.A[i][1]);
+                a.b0 = dt * ark.b[0]; a.b1 = dt * ark.b[1];
+                a.p = P;
+            }
+            HIPCHK(c, launch_ark_rhs(hevi_params(c), a, c->stream));
             const double *x0 = nullptr;
             if (guess) {
-                st = mlp_guess(guess, c, dt * ark.At[i][i], R, hevi_arr(c, 9), hevi_arr(c, 10));
+                st = mlp_guess(guess, c, dt * ark.At[i][i], R, hevi_arr(c, 7), hevi_arr(c, 8));
                 if (st) return st;
-                x0 = hevi_arr(c, 10);
+                x0 = hevi_arr(c, 8);
             }
             HIPCHK(c, run_gmres(c, dt * ark.At[i][i], R, x0, Q[i], opts, c->hiters + (i - 1) * ncol));
         }
-        HIPCHK(c, run_stage(c, t + ark.c[i] * dt, Q[i], nullptr, S[i], 0.0, 0.0, 1.0));
-        if (i < 2) HIPCHK(c, launch_lv_apply(hevi_params(c), Q[i], Lv[i], c->stream));
+        if (i < 2) HIPCHK(c, run_stage(c, t + ark.c[i] * dt, Q[i], nullptr, S[i], 0.0, 0.0, 1.0));
     }
-    LinComb lc{};
-    for (int j = 0; j < 3; ++j) { lc.src[j] = S[j]; lc.c[j] = dt * ark.b[j]; }
-    HIPCHK(c, launch_axpy_multi(n, Q1, 3, lc, Q1, c->stream));
+    // q^{n+1} = P + dt b_3 S(Q_3)
+    HIPCHK(c, run_stage(c, t + ark.c[2] * dt, Q[2], P, Q[0], 1.0, 0.0, dt * ark.b[2]));
     return gather_stats(c, c->hiters, 2, stats);
 }
 
