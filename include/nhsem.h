@@ -359,8 +359,8 @@ nh_status nh_hevi_last_solves(nh_ctx *ctx, const double **R2, const double **X2,
  * ------------------------------------------------------------------ */
 
 /* Device workspace of nh_global_solve and nh_imex3d_step for a restart
-   length (restart + 1 Krylov vectors, restart preconditioned vectors, one
-   scratch vector and, for the step, eight state-sized arrays, 5U doubles
+   length (restart + 1 Krylov vectors, restart preconditioned vectors
+   and, for the step, eight state-sized arrays, 5U doubles
    each; plus the block partial sums, the solver's device state and the
    operands of the column preconditioner). */
 nh_status nh_imex3d_workspace_bytes(const nh_ctx *ctx, int32_t restart, size_t *bytes);

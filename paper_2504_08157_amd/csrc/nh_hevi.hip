@@ -69,14 +69,20 @@ __global__ void __launch_bounds__(256) lv_apply_kernel(HeviParams h, const doubl
 }
 
 // ---------------------------------------------------------------- combinations
-// out = base + sum_j c[j] * src[j] (j < nsrc), elementwise on [5][U].
+// out = base + sum_j c[j] * src[j] (j < nsrc), elementwise on [5][U]; out2, if
+// given, the same with c2.
 __global__ void axpy_multi_kernel(long n, const double *__restrict__ base, int nsrc, LinComb lc,
-                                  double *__restrict__ out)
+                                  double *__restrict__ out, double *__restrict__ out2)
 {
     for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        double r = base[i];
-        for (int j = 0; j < nsrc; ++j) r += lc.c[j] * lc.src[j][i];
+        double r = base[i], r2 = r;
+        for (int j = 0; j < nsrc; ++j) {
+            const double v = lc.src[j][i];
+            r += lc.c[j] * v;
+            r2 += lc.c2[j] * v;
+        }
         out[i] = r;
+        if (out2) out2[i] = r2;
     }
 }
 
@@ -1169,10 +1175,11 @@ hipError_t launch_ark_rhs(const HeviParams &h, const ArkRhs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb &lc, double *out,
+hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb &lc, double *out, double *out2,
                              hipStream_t s)
 {
-    hipLaunchKernelGGL(axpy_multi_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, n, base, nsrc, lc, out);
+    hipLaunchKernelGGL(axpy_multi_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, n, base, nsrc, lc, out,
+                       out2);
     return hipGetLastError();
 }
 

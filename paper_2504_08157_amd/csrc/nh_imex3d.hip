@@ -25,7 +25,8 @@
 namespace nh {
 
 // out[f] = a x[f] + c (L x)[f] at every node, all of L in one walk (out may
-// not alias x).  Walls: u rows zero at x walls, v rows at y walls, w rows at
+// not alias x); RES: out = b - that, and
+// part[workgroup] = the sum of its squares.  Walls: u rows zero at x walls, v rows at y walls, w rows at
 // the bottom and top.  A workgroup of 64 x 8 lattice columns walks a chunk
 // of kz levels.  Per level it stages the planes of u, v and p'_L of its
 // tile plus an N-wide x/y halo in LDS (two buffers, one barrier per level)
@@ -40,7 +41,8 @@ namespace nh {
 // workgroups share a CU, so registers are held to 128 for N <= 4 (the y stencil
 // row, one per wave, is in scalar registers; node offsets are 32 bits on uniform
 // level bases), and that the chunks spread evenly over the CUs (l3_levels).
-// 256 x 256 x 41 nodes, N = 4: 55 us (85 before), 41 at the rate of a copy.
+// 256 x 256 x 41 nodes, N = 4: 55 us (85 before), 41 at the rate of a copy; the
+// residual form 96 us, where L and a combination with norms took 55 + 62.
 constexpr int kL3TX = 64, kL3TY = 8, kL3P = 1;
 
 __device__ __forceinline__ int l3_xcd_block(int b, int n)
@@ -60,14 +62,17 @@ __device__ __forceinline__ void l3_unrolled(F &&f)
 
 // (lev and gz are h.lev and h.hv.gz passed again as restrict pointers so
 // that their per-level values are read with scalar loads)
-template <int N>
+template <int N, bool RES>
 __global__ void __launch_bounds__(kL3TX * kL3TY, N <= 4 ? 4 : 2) l3_tile_kernel(L3Params h, const double *__restrict__ x,
                                                                 double *out, double a, double c,
                                                                 const double *__restrict__ lev,
                                                                 const double *__restrict__ gz, int kz,
-                                                                const int *gate)
+                                                                const int *gate,
+                                                                const double *__restrict__ b,
+                                                                double *__restrict__ part)
 {
     if (gate && *gate == 0) return;
+    double norm2 = 0.0;
     constexpr int NC = 2 * N + 1, PX = kL3TX + 2 * N, PY = kL3TY + 2 * N, PS = PX * PY;
     constexpr int NT = kL3TX * kL3TY, NH = (PS - NT + NT - 1) / NT, P = kL3P;   // NH: halo nodes per thread
     __shared__ double tile[2][3][PS];   // u, v, p'_L
@@ -209,13 +214,37 @@ __global__ void __launch_bounds__(kL3TX * kL3TY, N <= 4 ? 4 : 2) l3_tile_kernel(
             if (k == 0 || k == nz - 1) Lw = 0.0;
             if (own && k < ke) {
                 double *ol = out + (long)k * nxy;
-                ol[col] = a * xr + c * Lr;
-                (ol + U)[col] = a * xu + c * Lu;
-                (ol + 2 * U)[col] = a * xv + c * Lvv;
-                (ol + 3 * U)[col] = a * xw + c * Lw;
-                (ol + 4 * U)[col] = a * xt + c * Lt;
+                if constexpr (RES) {
+                    const double v[5] = {a * xr + c * Lr, a * xu + c * Lu, a * xv + c * Lvv, a * xw + c * Lw,
+                                         a * xt + c * Lt};
+                    const double *bl = b + (long)k * nxy;
+#pragma unroll
+                    for (int f = 0; f < 5; ++f) {
+                        const double r = (bl + f * U)[col] - v[f];
+                        norm2 += r * r;
+                        (ol + f * U)[col] = r;
+                    }
+                } else {
+                    ol[col] = a * xr + c * Lr;
+                    (ol + U)[col] = a * xu + c * Lu;
+                    (ol + 2 * U)[col] = a * xv + c * Lvv;
+                    (ol + 3 * U)[col] = a * xw + c * Lw;
+                    (ol + 4 * U)[col] = a * xt + c * Lt;
+                }
             }
         });
+    }
+    if constexpr (RES) {
+        __shared__ double red[NT / 64];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) norm2 += __shfl_xor(norm2, o);
+        if (tx == 0) red[ty] = norm2;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double r = 0.0;
+            for (int w = 0; w < NT / 64; ++w) r += red[w];
+            part[blockIdx.x] = r;
+        }
     }
 }
 
@@ -241,21 +270,36 @@ static int l3_levels(int tiles, int nz, int N)
     return kz;
 }
 
-hipError_t launch_l3(const L3Params &h, const double *x, double *out, double a, double c, hipStream_t s,
-                     const int *gate)
+int l3_max_blocks(int nx, int ny, int nz)
+{
+    return ((nx + kL3TX - 1) / kL3TX) * ((ny + kL3TY - 1) / kL3TY) * nz;
+}
+
+template <bool RES>
+static hipError_t launch_l3_form(const L3Params &h, const double *x, double *out, double a, double c, hipStream_t s,
+                                 const int *gate, const double *b, double *part, int *blocks)
 {
     const int ntx = (h.nx + kL3TX - 1) / kL3TX, nty = (h.ny + kL3TY - 1) / kL3TY;
     const int kz = l3_levels(ntx * nty, h.nz, h.N), nkc = (h.nz + kz - 1) / kz;
     const dim3 grid((unsigned)(ntx * nty * nkc)), blk(kL3TX * kL3TY);
+    if (blocks) *blocks = ntx * nty * nkc;
     switch (h.N) {
-    case 2: hipLaunchKernelGGL(l3_tile_kernel<2>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
-    case 3: hipLaunchKernelGGL(l3_tile_kernel<3>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
-    case 4: hipLaunchKernelGGL(l3_tile_kernel<4>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
-    case 5: hipLaunchKernelGGL(l3_tile_kernel<5>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
-    case 6: hipLaunchKernelGGL(l3_tile_kernel<6>, grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate); break;
+#define NH_L3(NN)                                                                                              \
+    case NN:                                                                                                   \
+        hipLaunchKernelGGL((l3_tile_kernel<NN, RES>), grid, blk, 0, s, h, x, out, a, c, h.lev, h.hv.gz, kz, gate, \
+                           b, part);                                                                           \
+        break;
+        NH_L3(2) NH_L3(3) NH_L3(4) NH_L3(5) NH_L3(6)
+#undef NH_L3
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_l3(const L3Params &h, const double *x, double *out, double a, double c, hipStream_t s,
+                     const int *gate)
+{
+    return launch_l3_form<false>(h, x, out, a, c, s, gate, nullptr, nullptr, nullptr);
 }
 
 // ---- Krylov kernels on n-vectors.  Dot products are summed per block into
@@ -339,34 +383,30 @@ static void launch_dots(int nv, const double *V, long n, const double *x, double
     }
 }
 
+// (Each thread takes two elements 2 KB apart: 67 us on average over a 3D-IMEX step's
+// launches, 71 with one.)
 // y = s (w - sum_j c_j V_j) for j < nv, nv = *nvp when given, s = *sc when
-// given (else 1), coefficients c in device memory; with norm also part[0][b]
-// = block sums of (w - sum_j c_j V_j)^2.  y may alias w.
+// given (else 1), coefficients c in device memory.  y may alias w.
 __global__ void __launch_bounds__(kKryThreads) kry_axpy_kernel(const double *__restrict__ V, long stride, int nv,
                                                                const int *nvp, const double *cf, const double *w,
-                                                               double *y, long n, const double *sc, int norm,
-                                                               double *__restrict__ part, const int *gate)
+                                                               double *y, long n, const double *sc, const int *gate)
 {
     if (gate && *gate == 0) return;
-    __shared__ double red[kKryThreads / 64];
     const int nvv = nvp ? *nvp : nv;
     const double s = sc ? *sc : 1.0;
-    double acc = 0.0;
-    for (long i = blockIdx.x * (long)kKryThreads + threadIdx.x; i < n; i += (long)gridDim.x * kKryThreads) {
-        double v = w[i];
+    constexpr int UF = 2;
+    for (long i0 = blockIdx.x * (long)(kKryThreads * UF) + threadIdx.x; i0 < n;
+         i0 += (long)gridDim.x * (kKryThreads * UF)) {
+        const bool two = i0 + kKryThreads < n;
+        const long i1 = two ? i0 + kKryThreads : i0;
+        double v0 = w[i0], v1 = w[i1];
 #pragma unroll 4
-        for (int j = 0; j < nvv; ++j) v -= cf[j] * V[j * stride + i];
-        acc += v * v;
-        y[i] = s * v;
-    }
-    if (!norm) return;
-    const double t = kry_wave_sum(acc);
-    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double r = 0.0;
-        for (int q = 0; q < kKryThreads / 64; ++q) r += red[q];
-        part[blockIdx.x] = r;
+        for (int j = 0; j < nvv; ++j) {
+            v0 -= cf[j] * V[j * stride + i0];
+            v1 -= cf[j] * V[j * stride + i1];
+        }
+        y[i0] = s * v0;
+        if (two) y[i1] = s * v1;
     }
 }
 
@@ -412,22 +452,29 @@ __global__ void __launch_bounds__(kKryCtl) g3_begin_kernel(G3State *st, const do
     st->ncols = 0;
     st->iters = 0;
     st->relres = 0.0;
-    st->one = 1.0;
     st->zero = 0.0;
     g3_publish(st, hs);
 }
 
-// Start of a cycle: beta = ||r|| from the partials of the residual; the solve
+// Start of a cycle: beta = ||r|| from the nb partials of the residual; the solve
 // ends when beta <= rtol ||b||, else (unless this is the final check) the
-// Arnoldi process starts from V_0 = r / beta.
-__global__ void __launch_bounds__(kKryCtl) g3_cycle_kernel(G3State *st, const double *__restrict__ part,
-                                                           double rtol, int final, G3Status *hs)
+// Arnoldi process starts from V_0 = r / beta.  With a preconditioner, the only
+// other reader of V_0, V_0 holds r and its users scale it by v0s = 1 / beta, which
+// saves a pass over it.
+__global__ void __launch_bounds__(kKryCtl) g3_cycle_kernel(G3State *st, const double *__restrict__ part, int nb,
+                                                           double rtol, int final, int precond, G3Status *hs)
 {
     if (st->open == 0) return;
-    __shared__ double red[1];
-    kry_reduce(part, 1, red);
+    __shared__ double red[kKryCtl / 64];
+    double r2 = 0.0;
+    for (int i = threadIdx.x; i < nb; i += kKryCtl) r2 += part[i];
+    r2 = kry_wave_sum(r2);
+    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = r2;
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    const double beta = sqrt(red[0]), bn = st->bn;
+    r2 = 0.0;
+    for (int w = 0; w < kKryCtl / 64; ++w) r2 += red[w];
+    const double beta = sqrt(r2), bn = st->bn;
     st->relres = beta / bn;
     st->ncols = 0;
     st->pass2 = 0;
@@ -437,6 +484,7 @@ __global__ void __launch_bounds__(kKryCtl) g3_cycle_kernel(G3State *st, const do
     } else {
         st->go = final ? 0 : 1;
         st->scale = 1.0 / beta;
+        st->v0s = precond ? st->scale : 1.0;
         st->gv[0] = beta;
         for (int i = 1; i <= kG3MaxRestart; ++i) st->gv[i] = 0.0;
     }
@@ -457,12 +505,13 @@ __global__ void __launch_bounds__(kKryCtl) g3_column_kernel(G3State *st, const d
     __shared__ double red[kKryMaxV + 1];
     kry_reduce(part, j + 2, red);
     if (threadIdx.x != 0) return;
+    red[0] *= st->v0s;
     double h2 = 0.0;
     for (int i = 0; i <= j; ++i) h2 += red[i] * red[i];
     const double w2 = red[j + 1];
     double k2 = w2 - h2;
     if (pass == 1) {
-        for (int i = 0; i <= j; ++i) st->coef[i] = red[i];
+        for (int i = 0; i <= j; ++i) st->coef[i] = i == 0 ? red[0] * st->v0s : red[i];
         if (!(k2 >= 1e-4 * w2)) {   // second pass
             for (int i = 0; i <= j; ++i) st->hc[i] = red[i];
             st->pass2 = 1;
@@ -473,7 +522,7 @@ __global__ void __launch_bounds__(kKryCtl) g3_column_kernel(G3State *st, const d
         st->pass2 = 0;
     } else {
         for (int i = 0; i <= j; ++i) {
-            st->coef[i] = red[i];
+            st->coef[i] = i == 0 ? red[0] * st->v0s : red[i];
             st->hc[i] += red[i];
         }
     }
@@ -536,10 +585,10 @@ struct Kry {
     }
     // y = sc (x - sum_j cf_j V_j)
     void axpy(const double *V, int nv, const int *nvp, const double *cf, const double *x, double *y,
-              const double *sc, bool norm, const int *gate)
+              const double *sc, const int *gate)
     {
         hipLaunchKernelGGL(kry_axpy_kernel, dim3(kKryBlocks), dim3(kKryThreads), 0, s, V, n, nv, nvp, cf, x, y, n, sc,
-                           norm ? 1 : 0, w.part, gate);
+                           gate);
     }
 };
 
@@ -685,9 +734,11 @@ __global__ void __launch_bounds__(kPcThreads) pc_setup_kernel(HeviParams h, doub
 template <int NT, int HB>
 __global__ void __launch_bounds__(256) pc_apply_kernel(HeviParams h, double alpha, const double *__restrict__ v,
                                                        double *__restrict__ z, const double *__restrict__ pack,
-                                                       const double *__restrict__ lev, const int *gate)
+                                                       const double *__restrict__ lev, const int *gate,
+                                                       const double *scale)
 {
     if (gate && *gate == 0) return;
+    const double sc = scale ? *scale : 1.0;
     typedef double double4v __attribute__((ext_vector_type(4)));
     constexpr int S = 4 * NT, NB = pc_band(HB);
     const int lane = threadIdx.x % 64, q = lane / 16;
@@ -706,13 +757,13 @@ __global__ void __launch_bounds__(256) pc_apply_kernel(HeviParams h, double alph
     for (int s = 0; s < S; ++s) {
         const int k = 4 * s + q;
         const long o = (long)(k < nz ? k : nz - 1) * nxy;
-        br[s] = x[o];
+        br[s] = sc * x[o];
         if constexpr (kUvFirst) {
-            bu[s] = x[U + o];
-            bv[s] = x[2 * U + o];
+            bu[s] = sc * x[U + o];
+            bv[s] = sc * x[2 * U + o];
         }
-        bw[s] = x[3 * U + o];
-        bt[s] = x[4 * U + o];
+        bw[s] = sc * x[3 * U + o];
+        bt[s] = sc * x[4 * U + o];
     }
     const double *pm = pack + lane, *pd = pack + (long)NT * S * 64 + lane;
     // acc = D u over the levels of tile T
@@ -787,8 +838,8 @@ __global__ void __launch_bounds__(256) pc_apply_kernel(HeviParams h, double alph
             const int k = 4 * s + q;
             if (own && k < nz) {
                 const long o = (long)k * nxy;
-                y[U + o] = x[U + o];
-                y[2 * U + o] = x[2 * U + o];
+                y[U + o] = sc * x[U + o];
+                y[2 * U + o] = sc * x[2 * U + o];
             }
         }
     }
@@ -803,17 +854,19 @@ static hipError_t launch_pc_setup(const L3Params &h, double alpha, double *pack,
 
 template <int NT>
 static hipError_t launch_pc_apply(int nt, const L3Params &h, double alpha, const double *v, double *z,
-                                  const double *pack, const int *gate, hipStream_t s)
+                                  const double *pack, const int *gate, const double *scale, hipStream_t s)
 {
     if constexpr (NT > kPcMaxTiles) {
         return hipErrorInvalidValue;
     } else {
-        if (nt != NT) return launch_pc_apply<NT + 1>(nt, h, alpha, v, z, pack, gate, s);
+        if (nt != NT) return launch_pc_apply<NT + 1>(nt, h, alpha, v, z, pack, gate, scale, s);
         const dim3 grid((unsigned)(((long)h.nx * h.ny + 63) / 64)), blk(256);
         if (pc_halo(h.N) == 1)
-            hipLaunchKernelGGL((pc_apply_kernel<NT, 1>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate);
+            hipLaunchKernelGGL((pc_apply_kernel<NT, 1>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate,
+                               scale);
         else
-            hipLaunchKernelGGL((pc_apply_kernel<NT, 2>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate);
+            hipLaunchKernelGGL((pc_apply_kernel<NT, 2>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate,
+                               scale);
         return hipGetLastError();
     }
 }
@@ -835,22 +888,22 @@ hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const doubl
     *iters = 0;
     *relres = 0.0;
     if (precond && !pc_ready && (e = launch_pc_setup(h, alpha, w.pc, s)) != hipSuccess) return e;
-    // ||b||, x = x0 (or b); x = 0 when b = 0
+    // ||b||; the first cycle starts from x0 (or b) and writes x; x = 0 when b = 0
     k.dots(V, 0, b, nullptr);
     hipLaunchKernelGGL(g3_begin_kernel, dim3(1), dim3(kKryCtl), 0, s, st, (const double *)w.part, w.status_dev);
-    if (x0 != x) k.axpy(V, 0, nullptr, nullptr, x0 ? x0 : b, x, nullptr, false, nullptr);
-    k.axpy(V, 0, nullptr, nullptr, x, x, &st->zero, false, &st->bzero);
+    const double *xs = x0 ? x0 : b;
     if ((e = hipGetLastError()) != hipSuccess) return e;
     auto mark = [&](int i) { return hipEventRecord(w.ev[i & 1], s); };
     for (int cyc = 0; cyc <= max_restarts + 1; ++cyc) {
         const bool final = cyc == max_restarts + 1;
-        // r = b - (x - alpha L x) into V_0, ||r||, then V_0 = r / ||r||
-        if ((e = launch_l3(h, x, w.t, 1.0, -alpha, s, &st->open)) != hipSuccess) return e;
-        k.axpy(w.t, 1, nullptr, &st->one, b, V, nullptr, true, &st->open);
-        hipLaunchKernelGGL(g3_cycle_kernel, dim3(1), dim3(kKryCtl), 0, s, st, (const double *)w.part, rtol,
-                           final ? 1 : 0, w.status_dev);
+        // V_0 = r = b - (x - alpha L x) and the partials of ||r||
+        int nb = 0;
+        if ((e = launch_l3_form<true>(h, xs, V, 1.0, -alpha, s, &st->open, b, w.part, &nb)) != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(g3_cycle_kernel, dim3(1), dim3(kKryCtl), 0, s, st, (const double *)w.part, nb, rtol,
+                           final ? 1 : 0, precond ? 1 : 0, w.status_dev);
         if (final) break;
-        k.axpy(V, 0, nullptr, nullptr, V, V, &st->scale, false, &st->go);
+        if (!precond) k.axpy(V, 0, nullptr, nullptr, V, V, &st->scale, &st->go);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = mark(0)) != hipSuccess) return e;
         bool waited = false;
@@ -865,7 +918,9 @@ hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const doubl
             const double *zj = vj;
             if (precond) {
                 double *zz = w.Z + (long)j * n;
-                if ((e = launch_pc_apply<1>((h.nz + 15) / 16, h, alpha, vj, zz, w.pc, &st->go, s)) != hipSuccess) return e;
+                if ((e = launch_pc_apply<1>((h.nz + 15) / 16, h, alpha, vj, zz, w.pc, &st->go,
+                                            j == 0 ? &st->v0s : nullptr, s)) != hipSuccess)
+                    return e;
                 zj = zz;
             }
             if ((e = launch_l3(h, zj, vn, 1.0, -alpha, s, &st->go)) != hipSuccess) return e;
@@ -873,21 +928,24 @@ hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const doubl
             k.dots(V, j + 1, vn, &st->go);
             hipLaunchKernelGGL(g3_column_kernel, dim3(1), dim3(kKryCtl), 0, s, st, (const double *)w.part, j, m, rtol,
                                1, w.status_dev);
-            k.axpy(V, j + 1, nullptr, st->coef, vn, vn, &st->scale, false, &st->go);
+            k.axpy(V, j + 1, nullptr, st->coef, vn, vn, &st->scale, &st->go);
             k.dots(V, j + 1, vn, &st->pass2);
             hipLaunchKernelGGL(g3_column_kernel, dim3(1), dim3(kKryCtl), 0, s, st, (const double *)w.part, j, m, rtol,
                                2, w.status_dev);
-            k.axpy(V, j + 1, nullptr, st->coef, vn, vn, &st->scale, false, &st->pass2);
+            k.axpy(V, j + 1, nullptr, st->coef, vn, vn, &st->scale, &st->pass2);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if ((e = mark(j + 1)) != hipSuccess) return e;
         }
         if (!waited && (e = hipEventSynchronize(w.ev[0])) != hipSuccess) return e;
         // x += Z y over the cycle's columns
         hipLaunchKernelGGL(g3_end_kernel, dim3(1), dim3(64), 0, s, st);
-        k.axpy(precond ? w.Z : V, 0, &st->ncols, st->coef, x, x, nullptr, false, &st->ncols);
+        k.axpy(precond ? w.Z : V, 0, &st->ncols, st->coef, xs, x, nullptr, cyc == 0 ? nullptr : &st->ncols);
+        xs = x;
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (w.status->open == 0) break;
     }
+    k.axpy(V, 0, nullptr, nullptr, x, x, &st->zero, &st->bzero);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
     *iters = w.status->iters;
     *relres = w.status->relres;

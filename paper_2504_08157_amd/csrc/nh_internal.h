@@ -159,7 +159,7 @@ struct GmresArgs {
 constexpr int kMaxComb = 6;
 struct LinComb {
     const double *src[kMaxComb];
-    double c[kMaxComb];
+    double c[kMaxComb], c2[kMaxComb];   // of out, of out2
 };
 
 // r = q1 + c0 s0 + d0 L_v q1 [+ c1 s1 + d1 L_v q2] on [5][U]; with q2 also
@@ -178,7 +178,7 @@ hipError_t launch_lv_apply(const HeviParams &h, const double *x, double *y, hipS
 // (I - alpha L_v) x = b at x3 = (rho', w, theta') as [3][U].
 hipError_t launch_lv_resid(const HeviParams &h, double alpha, const double *b, const double *x3, double *y,
                            hipStream_t s);
-hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb &lc, double *out,
+hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb &lc, double *out, double *out2,
                              hipStream_t s);
 hipError_t launch_gmres(const HeviParams &h, const GmresArgs &g, hipStream_t s);
 // The forms with z-elements on lanes: columns of up to 16 elements, restart
@@ -214,7 +214,8 @@ struct G3State {
     double cs[kG3MaxRestart], sn[kG3MaxRestart], gv[kG3MaxRestart + 1];
     double hc[kG3MaxRestart + 1];     // current column after the first Gram-Schmidt pass
     double coef[kG3MaxRestart + 1];   // coefficients of the next combination
-    double scale, one, zero, bn, relres;
+    double scale, zero, bn, relres;
+    double v0s;  // scale of V_0 (1 where V_0 is normalised itself)
     int go;      // the current cycle's Arnoldi process continues
     int pass2;   // the current column takes a second Gram-Schmidt pass
     int open;    // rtol not met yet
@@ -231,8 +232,7 @@ struct G3Status {
 struct G3Work {
     double *V;      // (restart + 1) Krylov vectors of 5U
     double *Z;      // restart preconditioned vectors (flexible GMRES)
-    double *t;      // one 5U vector
-    double *part;   // [35][1024] block partial sums, quantity-major
+    double *part;   // [35][1024] block partial sums, quantity-major; or one per workgroup of the residual
     double *pc;     // operands of the column preconditioner (g3_precond_bytes)
     G3State *state;                 // device
     G3Status *status_dev;           // host-mapped status, device address
@@ -243,6 +243,7 @@ struct G3Work {
 // flag) nothing is done while it is 0
 hipError_t launch_l3(const L3Params &h, const double *x, double *out, double a, double c, hipStream_t s,
                      const int *gate = nullptr);
+int l3_max_blocks(int nx, int ny, int nz);
 size_t g3_precond_bytes(int nz, int N);
 // (I - alpha L) x = b by restarted GMRES(m); iters = Arnoldi steps, relres =
 // final ||b - A x|| / ||b||

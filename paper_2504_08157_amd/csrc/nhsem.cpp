@@ -1219,9 +1219,8 @@ static L3Params l3_params(const nh_ctx *c)
     return h;
 }
 
-// workspace: restart + 1 Krylov vectors, restart preconditioned vectors, one
-// scratch vector, partial sums, then (step only) the ARK2 arrays S_0..2,
-// L_0..1, Q_1..2, R
+// workspace: restart + 1 Krylov vectors, restart preconditioned vectors,
+// partial sums, then (step only) the ARK2 arrays S_0..1, P, L_0..1, Q_1..2, R
 static size_t g3_bytes(const nh_ctx *c, int restart, bool step, G3Work *w, double **ark, char *base)
 {
     const size_t nv = align_up(sizeof(double) * kNF * (size_t)c->U);
@@ -1230,8 +1229,7 @@ static size_t g3_bytes(const nh_ctx *c, int restart, bool step, G3Work *w, doubl
     G3Work g{};
     g.V = (double *)take(nv * (restart + 1));
     g.Z = (double *)take(nv * restart);
-    g.t = (double *)take(nv);
-    g.part = (double *)take(sizeof(double) * 1024 * 35);
+    g.part = (double *)take(sizeof(double) * std::max(1024 * 35, l3_max_blocks(c->n[0], c->n[1], c->n[2])));
     g.state = (G3State *)take(sizeof(G3State));
     g.pc = (double *)take(g3_precond_bytes(c->n[2], c->N));
     if (step)
@@ -1365,21 +1363,22 @@ nh_status nh_imex3d_step(nh_ctx *c, double t, double dt, const nh_gmres_opts *op
     const long n = kNF * (long)c->U;
     const L3Params h = l3_params(c);
     double *Q1 = c->q[0];
-    double *S[3] = {a[0], a[1], a[2]};
+    double *S[2] = {a[0], a[1]}, *P = a[2];
     double *Lx[2] = {a[3], a[4]};
     double *Q[3] = {Q1, a[5], a[6]};
     double *R = a[7];
     bool missed = false;
     for (int i = 0; i < 3; ++i) {
         if (i > 0) {
-            // R = q^n + dt sum_{j<i} [A_ij S_j + (At_ij - A_ij) L_j]
+            // R = q^n + dt sum_{j<i} [A_ij S_j + (At_ij - A_ij) L_j]; with the second
+            // one P = q^n + dt (b_1 S_1 + b_2 S_2)
             LinComb lc{};
             int ns = 0;
             for (int j = 0; j < i; ++j) {
-                lc.src[ns] = S[j]; lc.c[ns++] = dt * ark.A[i][j];
+                lc.src[ns] = S[j]; lc.c2[ns] = dt * ark.b[j]; lc.c[ns++] = dt * ark.A[i][j];
                 lc.src[ns] = Lx[j]; lc.c[ns++] = dt * (ark.At[i][j] - ark.A[i][j]);
             }
-            HIPCHK(c, launch_axpy_multi(n, Q1, ns, lc, R, c->stream));
+            HIPCHK(c, launch_axpy_multi(n, Q1, ns, lc, R, i == 2 ? P : nullptr, c->stream));
             int it = 0;
             double rr = 0.0;
             HIPCHK(c, gmres3d(h, w, dt * ark.At[i][i], R, R, Q[i], opts->restart, opts->max_restarts, opts->rtol,
@@ -1387,12 +1386,12 @@ nh_status nh_imex3d_step(nh_ctx *c, double t, double dt, const nh_gmres_opts *op
             g3_count(stats, it, rr, opts->rtol);
             missed = missed || !(rr <= opts->rtol);
         }
+        if (i == 2) break;
         HIPCHK(c, run_stage(c, t + ark.c[i] * dt, Q[i], nullptr, S[i], 0.0, 0.0, 1.0));
-        if (i < 2) HIPCHK(c, launch_l3(h, Q[i], Lx[i], 0.0, 1.0, c->stream));
+        HIPCHK(c, launch_l3(h, Q[i], Lx[i], 0.0, 1.0, c->stream));
     }
-    LinComb lc{};
-    for (int j = 0; j < 3; ++j) { lc.src[j] = S[j]; lc.c[j] = dt * ark.b[j]; }
-    HIPCHK(c, launch_axpy_multi(n, Q1, 3, lc, Q1, c->stream));
+    // q^{n+1} = P + dt b_3 S(Q_3)
+    HIPCHK(c, run_stage(c, t + ark.c[2] * dt, Q[2], P, Q1, 1.0, 0.0, dt * ark.b[2]));
     if (missed) return fail(c, NH_ENOCONV, "3D-IMEX step: a stage solve missed rtol");
     return NH_OK;
 }
