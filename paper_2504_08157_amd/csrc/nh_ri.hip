@@ -156,7 +156,7 @@ __device__ __forceinline__ double ri_edge2(int j, double eps)
     return __dmul_rn(b, b);
 }
 
-// (s, about sqrt(r2), and ie = 1 / eps give the first guess, the edges decide)
+// (s = sqrt(r2) and ie = 1 / eps give the first guess, the edges decide)
 __device__ __forceinline__ int ri_strip(double r2, double s, double ie, double eps, int ns)
 {
     if (!(r2 > 0.0) || !(r2 < ri_edge2(ns, eps))) return -1;
@@ -168,20 +168,34 @@ __device__ __forceinline__ int ri_strip(double r2, double s, double ie, double e
     return (ri_edge2(j, eps) < r2 && r2 < ri_edge2(j + 1, eps)) ? j : -1;
 }
 
-// 1 / sqrt(r2) to about an ulp: the hardware's first value and one step of third
-// order; outside the middle of the exponent range by sqrt and a division
-__device__ __forceinline__ double ri_rsqrt(double r2)
+// s = sqrt(r2) and y = 1 / s for the quotients by it: the hardware's first value of
+// 1 / sqrt, one step of third order, and a residual correction of s; outside the
+// middle of the exponent range by sqrt and a division
+__device__ __forceinline__ void ri_root(double r2, double &s, double &y)
 {
-    if (!(r2 > 1e-290 && r2 < 1e290)) return 1.0 / sqrt(r2);
-    double y = __builtin_amdgcn_rsq(r2);
+    if (!(r2 > 1e-290 && r2 < 1e290)) {
+        s = sqrt(r2);
+        y = 1.0 / s;
+        return;
+    }
+    y = __builtin_amdgcn_rsq(r2);
     const double e = __builtin_fma(-(r2 * y), y, 1.0);
-    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+    y = __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+    s = r2 * y;
+    s = __builtin_fma(__builtin_fma(-s, s, r2), 0.5 * y, s);
+}
+
+// c / s (y as above), corrected by its residual; an infinite c stays infinite
+__device__ __forceinline__ double ri_quotient(double c, double s, double y)
+{
+    const double q = c * y;
+    return isinf(q) ? q : __builtin_fma(__builtin_fma(-q, s, c), y, q);
 }
 
 // strip sums and counts of chunk b of level k, and its maximum horizontal
 // speed.  The levels go from the last to the first: the centroid pass leaves the
 // last ones in the Infinity Cache (10 us of a call).  Bound: FP64 arithmetic and
-// the LDS additions.  512 x 512 x 81 nodes, 50 strips: 98 us (152 with a division and
+// the LDS additions.  512 x 512 x 81 nodes, 50 strips: 103 us (152 with a division and
 // a root per node, divided indices and an LDS addition per node).
 __global__ void __launch_bounds__(kRiThreads) ri_strip_partial(RiParams p, const double *__restrict__ q,
                                                                 const double *__restrict__ center,
@@ -227,8 +241,10 @@ __global__ void __launch_bounds__(kRiThreads) ri_strip_partial(RiParams p, const
                 const double ui = uu[r], vi = vv[r];
                 um = fmax(um, ui * ui + vi * vi);   // the root of the largest at the end
                 const double dy = __dsub_rn(y[r], yc);
-                const double r2 = __dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), is = ri_rsqrt(r2);
-                const int j = ri_strip(r2, r2 * is, ie, p.eps, ns);
+                const double r2 = __dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy));
+                double s, y1;
+                ri_root(r2, s, y1);
+                const int j = ri_strip(r2, s, ie, p.eps, ns);
                 if (j != cur) {
                     flush();
                     cur = j;
@@ -237,7 +253,7 @@ __global__ void __launch_bounds__(kRiThreads) ri_strip_partial(RiParams p, const
                 }
                 if (j >= 0) {
                     // |u_h . e_theta|: the horizontal velocity less its radial part
-                    sum += fabs(vi * dx - ui * dy) * is;
+                    sum += ri_quotient(fabs(vi * dx - ui * dy), s, y1);
                     ++cnt;
                 }
             }
