@@ -171,6 +171,10 @@ struct ArkRhs {
 };
 hipError_t launch_ark_rhs(const HeviParams &h, const ArkRhs &a, hipStream_t s);
 
+// per workgroup of kIterBlocks: sum, maximum and number of missed (negative) step counts
+constexpr int kIterBlocks = 64;
+hipError_t launch_iter_stats(const int *it, long n, long long *out, hipStream_t s);
+
 size_t gmres_lds_bytes(int nz, int N, int restart);
 // y = L_v x on [5][U]; with uv false the u and v rows of y are left untouched
 hipError_t launch_lv_apply(const HeviParams &h, const double *x, double *y, hipStream_t s, bool uv = true);
