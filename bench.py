@@ -63,7 +63,7 @@ def measured_traffic(tile, counters=COUNTERS, src=KERNEL_SRC, key="traffic_bytes
 
 
 GMRES_COUNTERS = os.path.join(ROOT, "profiles", "gmres_column_hevi_96x96x16_N4_counters.txt")
-GMRES_SRC = os.path.join(ROOT, "paper_2504_08157_amd", "csrc", "nh_hevi.hip")
+GMRES_SRC = os.path.join(ROOT, "paper_2504_08157_amd", "csrc", "nh_colgmres.hip")
 # MI355X vector FP64: 256 CUs x 4 SIMDs x 16 lanes x 2 flops x 2.4 GHz; a
 # wave64 VALU instruction occupies its SIMD for 4 cycles
 FP64_VALU_PEAK_TFLOPS = 78.6
@@ -73,7 +73,7 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 def gmres_counters(form):
     """Per column and Arnoldi step of the column GMRES kernel of `form`
     ("full" or "schur"): VALU wave instructions and executed FP64 flops from
-    the committed SQ counter summary, or None when nh_hevi.hip differs from
+    the committed SQ counter summary, or None when nh_colgmres.hip differs from
     the profiled source."""
     import hashlib
     try:
