@@ -66,8 +66,8 @@ __device__ __forceinline__ void ri_chunk(const RiParams &p, int b, B &&begin, R 
     const int lane = threadIdx.x % 64;
     for (int task = threadIdx.x / 64; task < cb * rg; task += kRiThreads / 64) {
         const int c = 64 * (task % cb) + lane, r0 = task / cb * per;
+        if (c >= nx) continue;   // lanes past the row have no column: nothing of the tables is theirs
         int r1 = r0 + per < nr ? r0 + per : nr;
-        if (c >= nx) r1 = r0;
         // the last row may end before this column
         if (r1 == nr && r1 > r0 && i0 + (long)(nr - 1) * nx + c >= i1) --r1;
         const int t = ix0 + c, wrap = t >= nx;
