@@ -751,7 +751,8 @@ __global__ void __launch_bounds__(64) gmres_reg_kernel(HeviParams h, GmresArgs g
                 if (sf[s] < 3) {
                     double acc = sx[lane + 64 * s];
 #pragma unroll
-                    for (int i = 0; i < M; ++i) acc += y[i] * V[i][s];
+                    for (int i = 0; i < M; ++i)
+                        if (i < jn) acc += y[i] * V[i][s];   // the vectors past an early stop were never written
                     sx[lane + 64 * s] = acc;
                 }
             }
@@ -1069,7 +1070,8 @@ __global__ void __launch_bounds__(64) gmres_schur_kernel(HeviParams h, GmresArgs
                 if (sk[s] > 0) {
                     double acc = sx[lane + 64 * s];
 #pragma unroll
-                    for (int i = 0; i < M; ++i) acc += y[i] * V[i][s];
+                    for (int i = 0; i < M; ++i)
+                        if (i < jn) acc += y[i] * V[i][s];   // the vectors past an early stop were never written
                     sx[lane + 64 * s] = acc;
                 }
             }
