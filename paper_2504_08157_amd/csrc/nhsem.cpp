@@ -46,7 +46,6 @@ struct nh_ctx {
     char *hws;
     size_t hws_bytes;
     int *hiters;
-    long long *hstat;
     float *gxf, *gyf;
     // tensor hyper-diffusion (caller-provided workspace, see nh_set_hyperdiffusion)
     bool hd_on;
@@ -511,7 +510,7 @@ nh_status nh_init_mesh(const nh_mesh_desc *mesh, const nh_physics *phys, void *d
     c->xl = (double *)(c->ws + L.xl);
     c->yl = (double *)(c->ws + L.yl);
     c->zl = (double *)(c->ws + L.zl);
-    c->hws = nullptr; c->hws_bytes = 0; c->hiters = nullptr; c->hstat = nullptr;
+    c->hws = nullptr; c->hws_bytes = 0; c->hiters = nullptr;
     c->gxf = (float *)(c->ws + L.gxf); c->gyf = (float *)(c->ws + L.gyf);
     c->lev = (double *)(c->ws + L.lev); c->hz2 = (double *)(c->ws + L.hz2);
     c->mx = (double *)(c->ws + L.mx); c->my = (double *)(c->ws + L.my); c->mz = (double *)(c->ws + L.mz);
@@ -851,7 +850,7 @@ size_t hevi_bytes(const nh_ctx *c)
 {
     const size_t fb = align_up(sizeof(double) * kNF * (size_t)c->U);
     const size_t ib = align_up(sizeof(int) * 2 * (size_t)c->n[0] * c->n[1]);
-    return kHeviArrays * fb + ib + align_up(sizeof(long long) * 3 * kIterBlocks);
+    return kHeviArrays * fb + ib;
 }
 
 double *hevi_arr(const nh_ctx *c, int i)
@@ -905,26 +904,17 @@ nh_status gather_stats(nh_ctx *c, const int *dev_iters, int nsolves, nh_solve_st
     st->columns = (int64_t)ncol;
     st->solves = nsolves;
     st->iters_total = 0; st->iters_max = 0; st->not_converged = 0;
-    if (c->hws) {
-        long long h[3 * kIterBlocks];
-        HIPCHK(c, launch_iter_stats(dev_iters, (long)(ncol * nsolves), c->hstat, c->stream));
-        HIPCHK(c, hipMemcpyAsync(h, c->hstat, sizeof h, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        for (int i = 0; i < kIterBlocks; ++i) {
-            st->iters_total += h[3 * i];
-            st->iters_max = std::max<int64_t>(st->iters_max, h[3 * i + 1]);
-            st->not_converged += h[3 * i + 2];
-        }
-    } else {
-        std::vector<int> h(ncol * nsolves);
-        HIPCHK(c, hipMemcpyAsync(h.data(), dev_iters, sizeof(int) * h.size(), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        for (int v : h) {
-            const int it = v >= 0 ? v : -v - 1;
-            st->iters_total += it;
-            if (it > st->iters_max) st->iters_max = it;
-            if (v < 0) ++st->not_converged;
-        }
+    // summed in the context's own scratch of the diagnostics (which synchronise, as this
+    // does): an attached HEVI workspace is not the column solve's to write
+    static_assert(3 * kIterBlocks <= 8 * kDiagBlocks && sizeof(long long) == sizeof(double), "diag_part holds them");
+    long long h[3 * kIterBlocks], *part = (long long *)c->diag_part;
+    HIPCHK(c, launch_iter_stats(dev_iters, (long)(ncol * nsolves), part, c->stream));
+    HIPCHK(c, hipMemcpyAsync(h, part, sizeof h, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    for (int i = 0; i < kIterBlocks; ++i) {
+        st->iters_total += h[3 * i];
+        st->iters_max = std::max<int64_t>(st->iters_max, h[3 * i + 1]);
+        st->not_converged += h[3 * i + 2];
     }
     return st->not_converged ? fail(c, NH_ENOCONV, "%lld column solves did not converge",
                                     (long long)st->not_converged)
@@ -1131,7 +1121,6 @@ nh_status nh_hevi_attach(nh_ctx *c, void *dev_ws, size_t bytes)
     c->hws = (char *)dev_ws;
     c->hws_bytes = bytes;
     c->hiters = (int *)(c->hws + kHeviArrays * align_up(sizeof(double) * kNF * (size_t)c->U));
-    c->hstat = (long long *)((char *)c->hiters + align_up(sizeof(int) * 2 * (size_t)c->n[0] * c->n[1]));
     return NH_OK;
 }
 
