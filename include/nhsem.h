@@ -314,8 +314,9 @@ nh_status nh_lv_apply(nh_ctx *ctx, const double *dev_x, double *dev_y);
 
 /* Solve (I - alpha L_v) x = b in every column by restarted matrix-free
    GMRES.  Columns of at most 16 elements with a restart of at most 20 are
-   solved two or four to a wavefront, one z-element per lane or lane pair;
-   others one wavefront per column (with restart 10 and 3 n_z <= 256 the
+   mostly solved two or four to a wavefront, one z-element per lane or lane
+   pair; others, and the shortest columns and smallest lattices, where it is
+   faster, one wavefront per column (with restart 10 and 3 n_z <= 256 the
    Krylov basis is held in registers, otherwise in LDS).  dev_b, dev_x:
    [5][U]; the u, v fields of x are copied from b.  dev_x0: initial guess of
    (rho', w, theta') as [3][U], or NULL for x0 = b.  dev_iters: optional

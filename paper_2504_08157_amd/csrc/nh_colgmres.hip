@@ -424,7 +424,10 @@ __device__ __forceinline__ void gmres_lanes(const Op &op, double al, double tol,
         // Least squares: lane k of a group takes column k of the Hessenberg
         // matrix of A and the rotations run over all columns at once
         // (rotation i from column i, broadcast over the group); a system that
-        // stopped at jn takes its first jn columns.
+        // stopped at jn takes its first jn columns.  The long form leaves out
+        // what lies past the last step any column of the wave took: 20 columns
+        // cost more than the steps of a short column do (10 do not, measured).
+        constexpr bool kAll = M <= kGmresRegM;
         double y[M];
         {
             double q[M + 1], gv[M + 1], idiag = 1.0;
@@ -437,25 +440,30 @@ __device__ __forceinline__ void gmres_lanes(const Op &op, double al, double tol,
             gv[0] = rn;
             static_for<M>([&](auto ic) __attribute__((always_inline)) {
                 constexpr int i = decltype(ic)::value;
-                const double a = G::template bcast<i>(q[i]), b = G::template bcast<i>(q[i + 1]);
-                const double d2 = a * a + b * b;
-                const double id = d2 > 0.0 ? inv_sqrt(d2) : 0.0;
-                const double c = d2 > 0.0 ? a * id : 1.0, sn = b * id;
-                if (ln == i && i < jn) idiag = id;
-                const double u = q[i], v = q[i + 1];
-                q[i] = c * u + sn * v;
-                q[i + 1] = c * v - sn * u;
-                gv[i + 1] = -sn * gv[i];
-                gv[i] = c * gv[i];
+                if (kAll || i < j) {
+                    const double a = G::template bcast<i>(q[i]), b = G::template bcast<i>(q[i + 1]);
+                    const double d2 = a * a + b * b;
+                    const double id = d2 > 0.0 ? inv_sqrt(d2) : 0.0;
+                    const double c = d2 > 0.0 ? a * id : 1.0, sn = b * id;
+                    if (ln == i && i < jn) idiag = id;
+                    const double u = q[i], v = q[i + 1];
+                    q[i] = c * u + sn * v;
+                    q[i + 1] = c * v - sn * u;
+                    gv[i + 1] = -sn * gv[i];
+                    gv[i] = c * gv[i];
+                }
             });
             static_for<M>([&](auto ic) __attribute__((always_inline)) {
                 constexpr int i = M - 1 - decltype(ic)::value;
-                const double yi = i < jn ? gv[i] * G::template bcast<i>(idiag) : 0.0;
-                y[i] = yi;
-                static_for<i>([&](auto kc) __attribute__((always_inline)) {
-                    constexpr int k = decltype(kc)::value;
-                    gv[k] -= yi * G::template bcast<i>(q[k]);
-                });
+                y[i] = 0.0;
+                if (kAll || i < j) {
+                    const double yi = i < jn ? gv[i] * G::template bcast<i>(idiag) : 0.0;
+                    y[i] = yi;
+                    static_for<i>([&](auto kc) __attribute__((always_inline)) {
+                        constexpr int k = decltype(kc)::value;
+                        gv[k] -= yi * G::template bcast<i>(q[k]);
+                    });
+                }
             });
         }
 #pragma unroll
@@ -1119,9 +1127,39 @@ void launch_forms(const HeviParams &h, const GmresArgs &g, hipStream_t s)
 
 }  // namespace
 
+// Which solves run here and which one column per wave (nh_hevi.hip).  A wave's
+// time in this file hardly depends on how many of its lanes have an element,
+// while the other forms get faster with fewer unknowns, and with a SIMD for
+// every column there it is the length of one solve that counts, not the
+// number of instructions.  So short columns and small lattices go there where
+// that measured faster; times there / here on columns of 1 to 16 elements,
+// 9 to 16384 columns, alpha 0.3 and 2, to 1e-8:
+//   full form, restart 10 (registers there, 3 n_z <= 256): up to 1024 columns 0.95-0.99,
+//     0.85-0.97, 0.77-0.9 and 0.68-0.99 at orders 2 to 5 up to the elements of the table
+//     (1.0-1.2 above); up to 2048 columns 0.82-0.94 (order 4) and 0.85-0.96 (5) up to
+//     half as many; with more 1.05-2.6.  Order 6: 0.61-0.95 up to 10 elements on any
+//     lattice (1.0 at up to 2048 of them, 10 elements), 0.92-1.29 above.
+//   restart 11 to 20: 1.0-5.5 while the lattice gives every wave slot one wave (four to a
+//     CU, at orders 5 and 6 three); on more columns 0.49-0.95 with one element, 0.64-1.05 with two,
+//     0.78-1.1 with three at restarts up to 16, and while few slots get a second wave
+//     0.81-0.95 with three and four (1.4 at orders 5 and 6 from 2304 columns on); 1.0-8.7 above.
+//   restart below 10: 1.05-11 but for order 6 on more than 2048 columns: 0.66-0.97 up to
+//     three elements, 0.7-0.93 up to six at restarts 1 to 3.
+//   Schur form: 1.0-4.4 but for order 6, up to 1024 columns of one or two elements: 0.9-0.99.
 bool gmres_lanes_ok(const HeviParams &h, const GmresArgs &g)
 {
-    return (h.nz - 1) / h.N <= kColElems && g.restart <= kGmresColM;
+    const int e = (h.nz - 1) / h.N, N = h.N;
+    const long ncol = (long)h.nx * h.ny;
+    if (e > kColElems || g.restart > kGmresColM) return false;
+    if (g.schur) return !(N == 6 && e <= 2 && ncol <= 1024);
+    if (g.restart > kGmresRegM)
+        return ncol <= (N <= 4 ? 2048 : 1536) || e > (ncol <= 2304 ? 4 : ncol <= 3072 || g.restart <= 16 ? 3 : 2);
+    if (g.restart < kGmresRegM) return N < 6 || ncol <= 2048 || e > (g.restart <= 3 ? 6 : 3);
+    if (3 * h.nz > 64 * kGmresRegSlots) return true;
+    if (N == 6) return e > 10;
+    static const int few[6] = {0, 0, 8, 10, 6, 12};
+    const int top = ncol <= 1024 ? few[N] : ncol <= 2048 && N >= 4 ? few[N] / 2 : 0;
+    return e > top;
 }
 
 hipError_t launch_gmres_lanes(const HeviParams &h, const GmresArgs &g0, hipStream_t s)

@@ -21,8 +21,8 @@
 // (unknown u on lane u mod 64), dot products are wave reductions, and a
 // column never waits for another column.  For m = 10 (and 3 n_z <= 256) the
 // Krylov basis lives in registers; otherwise in LDS.  These forms serve
-// columns of more than 16 elements and restarts above 20; the others run in
-// nh_colgmres.hip.
+// columns of more than 16 elements, restarts above 20 and the short columns
+// and small lattices of gmres_lanes_ok; the others run in nh_colgmres.hip.
 #include "nh_internal.h"
 
 #include <math.h>
@@ -1232,9 +1232,8 @@ hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb
 hipError_t launch_gmres(const HeviParams &h, const GmresArgs &g, hipStream_t s)
 {
     const long ncol = (long)h.nx * h.ny;
-    // up to 16 elements and restart 20: z-elements on lanes, two or four columns
-    // per wave (nh_colgmres.hip), 2.6 to 4.7 times faster than the forms here,
-    // which solve the taller columns and the longer restarts
+    // z-elements on lanes, two or four columns per wave (nh_colgmres.hip), where
+    // that is the faster form: on large lattices of 12 and 16 elements 2.6 to 4.7 times
     if (gmres_lanes_ok(h, g)) return launch_gmres_lanes(h, g, s);
     if (g.schur) {
         if (g.restart != kGmresRegM || h.nz - 2 > 64 * kGmresSchurSlots) return hipErrorInvalidValue;

@@ -186,7 +186,7 @@ hipError_t launch_axpy_multi(long n, const double *base, int nsrc, const LinComb
                              hipStream_t s);
 hipError_t launch_gmres(const HeviParams &h, const GmresArgs &g, hipStream_t s);
 // The forms with z-elements on lanes: columns of up to 16 elements, restart
-// lengths up to kGmresColM
+// lengths up to kGmresColM, where they are the faster ones
 bool gmres_lanes_ok(const HeviParams &h, const GmresArgs &g);
 hipError_t launch_gmres_lanes(const HeviParams &h, const GmresArgs &g, hipStream_t s);
 
