@@ -9,7 +9,8 @@ from paper_2504_08157_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nel,restart", [((3, 2, 4), 10), ((3, 2, 4), 20), ((2, 2, 18), 10)])
+@pytest.mark.parametrize("nel,restart", [((3, 2, 4), 10), ((3, 2, 4), 20), ((2, 2, 18), 10),
+                                         ((16, 8, 3), 10), ((16, 9, 3), 10)])
 def test_column_solve_leaves_the_workspace(nel, restart):
     import torch
     from paper_2504_08157_amd import nhsem
