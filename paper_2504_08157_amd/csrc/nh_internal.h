@@ -265,6 +265,7 @@ struct RiParams {
     const double *x, *y;           // lattice coordinates [n_x], [n_y]
     const double *mx, *my;         // assembled 1D masses
     double eps, xmid, ymid;        // strip width; centre of a level at rest
+    int rg, parts;                 // row groups of a chunk; parts of a strip's final sum (set by launch_ri)
 };
 struct RiWork {
     double *cpart;   // [n_z][nb][3] centroid partial sums

@@ -7,8 +7,8 @@
 // workgroup per (chunk, level): a reduction pass for the centre, then a
 // histogram pass (strip sums and counts in LDS) for the means.  Partial
 // results per workgroup are combined in a fixed order by small final
-// kernels; only the LDS histogram additions are unordered.  A wave takes 64
-// neighbouring columns and walks the rows of the chunk, so that no index is
+// kernels; only the LDS histogram additions are unordered.  Neighbouring
+// threads take neighbouring columns and walk rows of the chunk, so that no index is
 // divided per node, and a lane adds the nodes of one strip up in registers
 // until the strip changes: neighbouring rows mostly share it.  (Summing the
 // lanes of one strip across the wavefront before each LDS update was 2.8x
@@ -49,10 +49,31 @@ __device__ __forceinline__ double ri_block_max(double v, double *red)
     return r;
 }
 
+// Groups of rows that a chunk is cut into.  Its tasks, a column of a group each,
+// take the threads ceil(columns groups / threads) rounds of ceil(rows / groups) rows,
+// and about one and a half rows' worth of start and end each; tried are the groups that
+// fill 1 to 16 rounds.
+static int ri_row_groups(int nx, int ny, int nb)
+{
+    const long nxy = (long)nx * ny, chunk = (nxy + nb - 1) / nb, nc = chunk < nx ? chunk : nx;
+    const long nr = (chunk + nx - 1) / nx;
+    double best = 1e300;
+    long rg = 1;
+    for (int k = 1; k <= 16; ++k) {
+        long g = k * (long)kRiThreads / nc;
+        g = g < 1 ? 1 : g > nr ? nr : g;
+        const double t = (double)((nc * g + kRiThreads - 1) / kRiThreads) * ((double)((nr + g - 1) / g) + 1.5);
+        if (t < best) {
+            best = t;
+            rg = g;
+        }
+    }
+    return (int)rg;
+}
+
 // The columns of chunk b of a level: rows of nx consecutive columns from
-// the chunk's first one, cut into blocks of 64 (a wave's lanes) and, where
-// that gives fewer tasks than waves, into groups of rows.  For each task of
-// the wave: begin(ix) with the lane's x index, rows(i, iy, n) for n <= kRiRows
+// the chunk's first one, cut into p.rg groups of rows.  For each column of a
+// group that is the thread's: begin(ix) with its x index, rows(i, iy, n) for n <= kRiRows
 // rows (columns i, i + nx, ..., y indices iy, iy + 1, ...), end().
 template <typename B, typename R, typename E>
 __device__ __forceinline__ void ri_chunk(const RiParams &p, int b, B &&begin, R &&rows, E &&end)
@@ -60,16 +81,14 @@ __device__ __forceinline__ void ri_chunk(const RiParams &p, int b, B &&begin, R 
     const long nxy = (long)p.nx * p.ny, chunk = (nxy + p.nb - 1) / p.nb;
     const long i0 = b * chunk, i1 = i0 + chunk < nxy ? i0 + chunk : nxy;
     if (i0 >= i1) return;
-    const int nx = p.nx, ix0 = (int)(i0 % nx), iy0 = (int)(i0 / nx);
-    const int nr = (int)((i1 - i0 + nx - 1) / nx), cb = (nx + 63) / 64;
-    const int rg = cb >= 4 ? 1 : (4 + cb - 1) / cb, per = (nr + rg - 1) / rg;
-    const int lane = threadIdx.x % 64;
-    for (int task = threadIdx.x / 64; task < cb * rg; task += kRiThreads / 64) {
-        const int c = 64 * (task % cb) + lane, r0 = task / cb * per;
-        if (c >= nx) continue;   // lanes past the row have no column: nothing of the tables is theirs
+    const int nx = p.nx, ix0 = (int)(i0 % nx), iy0 = (int)(i0 / nx), nc = i1 - i0 < nx ? (int)(i1 - i0) : nx;
+    const int nr = (int)((i1 - i0 + nx - 1) / nx), per = (nr + p.rg - 1) / p.rg;
+    for (int task = threadIdx.x; task < nc * p.rg; task += kRiThreads) {
+        const int g = task / nc, c = task - g * nc, r0 = g * per;
         int r1 = r0 + per < nr ? r0 + per : nr;
         // the last row may end before this column
-        if (r1 == nr && r1 > r0 && i0 + (long)(nr - 1) * nx + c >= i1) --r1;
+        if (r1 == nr && i0 + (long)(nr - 1) * nx + c >= i1) --r1;
+        if (r0 >= r1) continue;
         const int t = ix0 + c, wrap = t >= nx;
         begin(wrap ? t - nx : t);
         long i = i0 + (long)r0 * nx + c;
@@ -309,7 +328,7 @@ __global__ void __launch_bounds__(kRiThreads) ri_strip_final(RiParams p, const d
     __shared__ int pc[kRiThreads];
     __shared__ long ra[kRiThreads / 64];
     const int k = blockIdx.x, ns = p.nstrips, t = threadIdx.x;
-    const int parts = ns < kRiThreads ? kRiThreads / ns : 1, w = ns < kRiThreads ? ns : kRiThreads;
+    const int parts = p.parts, w = ns < kRiThreads ? ns : kRiThreads;
     const int part = t / w, per = (p.nb + parts - 1) / parts;
     double best = -1.0;
     long at = -1;
@@ -381,9 +400,15 @@ __global__ void __launch_bounds__(kRiThreads) ri_max_final(RiParams p, const dou
 
 size_t ri_lds_bytes(int nstrips) { return (size_t)nstrips * (sizeof(double) + sizeof(int)); }
 
-hipError_t launch_ri(const RiParams &p, const double *q, bool center_given, double *center, double *ubar,
+hipError_t launch_ri(const RiParams &p0, const double *q, bool center_given, double *center, double *ubar,
                      int *count, double *result, const double *z, const RiWork &w, hipStream_t s)
 {
+    RiParams p = p0;
+    p.rg = ri_row_groups(p.nx, p.ny, p.nb);
+    // parts of a strip's sum: the threads there are, and no more than the additions that are
+    // left to one thread after them
+    p.parts = 1;
+    while (p.parts * p.parts < p.nb && (p.parts + 1) * p.nstrips <= kRiThreads) ++p.parts;
     const dim3 grid(p.nb, p.nz), blk(kRiThreads);
     if (!center_given) {
         hipLaunchKernelGGL(ri_centroid_partial, grid, blk, 0, s, p, q, w.cpart);

@@ -17,7 +17,7 @@ HOST = r"""
 #define __device__
 #define __forceinline__ inline
 struct { int x; } threadIdx;
-struct RiParams { int nx, ny, nb; };
+struct RiParams { int nx, ny, nb, rg; };
 %s
 int main(int argc, char **argv)
 {
@@ -25,6 +25,7 @@ int main(int argc, char **argv)
     p.nx = atoi(argv[1]);
     p.ny = atoi(argv[2]);
     p.nb = atoi(argv[3]);
+    p.rg = argc > 4 ? atoi(argv[4]) : ri_row_groups(p.nx, p.ny, p.nb);
     const long nxy = (long)p.nx * p.ny;
     std::vector<int> seen(nxy, 0);
     long out = 0, wrong = 0;
@@ -60,8 +61,9 @@ int main(int argc, char **argv)
 def _walk():
     src = open(SRC).read()
     consts = re.findall(r"^constexpr int kRi(?:Threads|Rows) = \d+;", src, re.M)
-    i = src.index("template <typename B, typename R, typename E>")
-    return "\n".join(consts) + "\n" + src[i:src.index("\n}\n", i) + 3]
+    funs = [src[i:src.index("\n}\n", i) + 3] for i in (src.index("static int ri_row_groups("),
+                                                       src.index("template <typename B, typename R, typename E>"))]
+    return "\n".join(consts + funs)
 
 
 @pytest.fixture(scope="module")
@@ -78,6 +80,9 @@ def replay(tmp_path_factory):
 @pytest.mark.parametrize("nx,ny,nb", [(2, 3, 1), (12, 10, 1), (24, 24, 1), (63, 7, 1), (64, 140, 3), (65, 282, 5),
                                       (129, 165, 6), (260, 200, 13), (402, 100, 10), (512, 512, 64), (4104, 7, 8),
                                       (7, 2000, 4), (65, 2, 9)])
-def test_columns_visited_once_inside_the_tables(replay, nx, ny, nb):
-    out = subprocess.run([replay, str(nx), str(ny), str(nb)], check=True, capture_output=True, text=True).stdout
+@pytest.mark.parametrize("rg", [None, 1, 2, 7, 4096])
+def test_columns_visited_once_inside_the_tables(replay, nx, ny, nb, rg):
+    """rg: the groups of rows, the library's own choice (None) and others, also more than rows."""
+    out = subprocess.run([replay, str(nx), str(ny), str(nb)] + ([] if rg is None else [str(rg)]), check=True,
+                         capture_output=True, text=True).stdout
     assert out.split() == ["0", "0", "0"], "indices outside, wrong coordinates, columns not visited once: " + out
