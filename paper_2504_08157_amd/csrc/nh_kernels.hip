@@ -530,7 +530,7 @@ __global__ void __launch_bounds__((StageShape<N, AX, AY>::NT)) stage_kernel(cons
 }
 
 // The same stage with each column cut into `nchunk` runs of elements, for
-// lattices with too few tiles for the chip (split_plan): workgroup
+// lattices with too few tiles for the chip (stage_plan): workgroup
 // chunk * tiles + tile, element run [chunk nelz / nchunk, (chunk + 1) nelz / nchunk).
 template <int N, int AX, int AY, typename T>
 __global__ void __launch_bounds__((StageShape<N, AX, AY>::NT)) stage_kernel_split(const StageParams p, int nchunk)
@@ -1298,14 +1298,19 @@ static void launch_split(int N, int precision, int shape, const StageParams &p, 
 // (a 40 x 40 x 16 order-4 lattice has 100 tiles for 256 CUs: 100 us per launch,
 // 58 with two runs per column; the 4 x 4 x 4 one 27 us, 11 with small tiles
 // and a run per element; a 40 x 40 x 16 order-5 one 251 us, 168 with the 20 x 10
-// tile).  The estimate below reproduces a sweep over 20 lattices, four
-// shapes and the runs per column to about 10 % in order: tau is measured per
-// order and shape on lattices that leave the chip idle, a workgroup costs
-// 3.5 us beside its elements (tables, the element below) and a launch 3 us,
-// the elements take up to 15 % longer as the chip fills, and small
-// workgroups that share a CU finish in 0.8 of their time alone.  A plan other
-// than whole columns of shape 0 is taken where it gains 6 % or more: the
-// 512 x 512 x 81 and 256 x 256 x 41 lattices (1024 and 256 tiles) keep it.
+// tile).  The estimate below orders the plans: tau is measured per order and
+// shape at FP64 on lattices that leave the chip idle, a workgroup costs
+// 3.5 us beside its elements (tables, the element below; a run of a split
+// column that waits for a CU 5.5) and a launch 3 us, the elements take up to
+// 15 % longer as the chip fills, and small workgroups that share a CU finish in
+// 0.8 of their time alone.  A plan other than whole columns of shape 0 is taken
+// where it gains 10 % or more (order 2, whose short elements the estimate
+// prices too high, 16 %): the 512 x 512 x 81 and 256 x 256 x 41 lattices (1024 and
+// 256 tiles) keep them.  FP32-mixed takes the same plan: its elements are faster
+// by about the same share in every shape.  Over 230 lattices, against whole
+// columns of shape 0: geometric mean 2.04x in FP64 and 1.94x in FP32-mixed (the
+// best plan of each 2.06x and 1.98x), the worst 0.97x; with 3.5 us throughout and
+// 6 % 2.04x and 1.93x, the worst 0.90x and 0.85x.  Over 260 others 1.99x and 1.90x.
 void stage_plan(int N, int nx, int ny, int nelz, int *shape, int *nchunk)
 {
     static const double tau[5][4] = {{3.2, 3.7, 4.5, 3.0}, {5.7, 6.1, 6.1, 3.8}, {6.0, 7.3, 4.9, 4.6},
@@ -1326,7 +1331,7 @@ void stage_plan(int N, int nx, int ny, int nelz, int *shape, int *nchunk)
             const int e = (nelz + z - 1) / z;                 // elements of the longest run
             if (z > 1 && (nelz + z - 2) / (z - 1) == e) continue;   // as long with fewer runs
             const double n = tiles * z, fill = n < 256.0 ? n / 256.0 : 1.0;
-            const double one = e * tau[N - 2][s] * (1.0 + 0.15 * fill) + 3.5;
+            const double one = e * tau[N - 2][s] * (1.0 + 0.15 * fill) + (z > 1 && s < 3 && n > 256.0 ? 5.5 : 3.5);
             double t;
             if (s == 3) {
                 const double m = n / 256.0;                   // several to a CU
@@ -1335,7 +1340,7 @@ void stage_plan(int N, int nx, int ny, int nelz, int *shape, int *nchunk)
                 t = one * (double)((long)((n + 255.0) / 256.0));
             }
             t += 3.0;
-            if (s == 0 && z == 1) best = 0.94 * t;
+            if (s == 0 && z == 1) best = (N == 2 ? 0.84 : 0.9) * t;
             else if (t < best) {
                 best = t;
                 *shape = s;
