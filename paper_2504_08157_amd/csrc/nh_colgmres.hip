@@ -27,10 +27,9 @@
 // with one column per wave, 225 VALU instructions per column and step
 // against 524, VALU active 59 % of the cycles.
 #include "nh_internal.h"
+#include "nh_lanes.h"
 
 #include <math.h>
-
-#include <utility>
 
 namespace nh {
 
@@ -38,61 +37,12 @@ namespace {
 
 constexpr int kColElems = 16;   // elements of a column, at most
 
-template <class F, int... J>
-__device__ __forceinline__ void static_for_impl(F &f, std::integer_sequence<int, J...>)
-{
-    (f(std::integral_constant<int, J>{}), ...);
-}
-// f(integral_constant<int, j>) for j = 0 .. n-1, in order
-template <int n, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    static_for_impl(f, std::make_integer_sequence<int, n>{});
-}
-
-__device__ __forceinline__ double join_d(unsigned lo, unsigned hi)
-{
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// DPP lane move; lanes without a source read 0.
-template <int CTRL>
-__device__ __forceinline__ double lane_move(double v)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
-    return join_d((unsigned)lo, (unsigned)hi);
-}
-constexpr int kSwapPair = 0xB1;   // quad_perm [1,0,3,2]: lane i <-> lane i ^ 1
 constexpr int kRowShl1 = 0x101;   // lane i <- lane i + 1, inside 16-lane rows
 constexpr int kRowShr1 = 0x111;   // lane i <- lane i - 1
 constexpr int kRowShr2 = 0x112;
 constexpr int kRowBcast = 0x150;  // every lane of a row <- lane L (0x150 + L)
 constexpr int kWaveShl1 = 0x130;  // lane i <- lane i + 1, over the wave
 constexpr int kWaveShr1 = 0x138;
-
-// every lane of a 16-lane row <- the sum over its row
-__device__ __forceinline__ double row_sum(double v)
-{
-    v += lane_move<kSwapPair>(v);
-    v += lane_move<0x4E>(v);   // quad_perm [2,3,0,1]
-    v += lane_move<0x141>(v);  // row_half_mirror
-    v += lane_move<0x140>(v);  // row_mirror
-    return v;
-}
-
-// gfx950 exchange of 16-lane rows between two registers:
-// a <- [a row 0, b row 0, a row 2, b row 2], b <- [a row 1, b row 1, a row 3, b row 3]
-__device__ __forceinline__ void swap_rows(double &a, double &b)
-{
-    const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
-    const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-    a = join_d(lo[0], hi[0]);
-    b = join_d(lo[1], hi[1]);
-}
 
 // Lane groups of a column: 16 lanes (a DPP row) or 32 (half the wave).
 // sum, sum2: one or two sums over the group, left in every lane;
@@ -115,10 +65,10 @@ struct Half32 {
     static constexpr int LANES = 32;
     static __device__ __forceinline__ void sum2(double &a, double &b)
     {
-        swap_rows(a, b);
+        swap16(a, b);
         a = row_sum(a + b);   // rows 0, 2: sums of a; rows 1, 3: sums of b
         b = a;
-        swap_rows(a, b);
+        swap16(a, b);
     }
     static __device__ __forceinline__ double sum(double a)
     {
@@ -130,7 +80,7 @@ struct Half32 {
     static __device__ __forceinline__ double bcast(double v)
     {
         double a = lane_move<kRowBcast + L % 16>(v), b = a;
-        swap_rows(a, b);      // a: row 0 (2) of the broadcast in rows 0, 1 (2, 3); b: row 1 (3)
+        swap16(a, b);      // a: row 0 (2) of the broadcast in rows 0, 1 (2, 3); b: row 1 (3)
         return L < 16 ? a : b;
     }
 };
@@ -142,12 +92,6 @@ __device__ __forceinline__ double inv_sqrt(double x)
     double y = __builtin_amdgcn_rsq(x);
     y = y + 0.5 * y * fma(-x * y, y, 1.0);
     return y + 0.5 * y * fma(-x * y, y, 1.0);
-}
-
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
 // The LGL derivative matrix in scalar registers: the host makes it exactly

@@ -24,10 +24,9 @@
 // columns of more than 16 elements, restarts above 20 and the short columns
 // and small lattices of gmres_lanes_ok; the others run in nh_colgmres.hip.
 #include "nh_internal.h"
+#include "nh_lanes.h"
 
 #include <math.h>
-
-#include <utility>
 
 namespace nh {
 
@@ -368,56 +367,7 @@ __global__ void __launch_bounds__(64) gmres_column_kernel(HeviParams h, GmresArg
 }
 
 // ---------------------------------------------------------------- GMRES, register basis
-// Wave-wide sums in registers (no LDS traffic): gfx950 lane swaps between
-// register pairs and DPP butterflies inside 16-lane rows.
-
-// DPP lane move with every source lane valid.
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-__device__ __forceinline__ double join_d(unsigned lo, unsigned hi)
-{
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// gfx950 lane swaps between two registers (one 16-lane row is a "row"):
-// swap32: a <- [a lanes 0-31, b lanes 0-31], b <- [a lanes 32-63, b lanes 32-63]
-// swap16: a <- [a row 0, b row 0, a row 2, b row 2], b <- [a row 1, b row 1, a row 3, b row 3]
-__device__ __forceinline__ void swap32(double &a, double &b)
-{
-    const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
-    const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-    a = join_d(lo[0], hi[0]);
-    b = join_d(lo[1], hi[1]);
-}
-
-__device__ __forceinline__ void swap16(double &a, double &b)
-{
-    const unsigned long long ua = (unsigned long long)__double_as_longlong(a);
-    const unsigned long long ub = (unsigned long long)__double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-    a = join_d(lo[0], hi[0]);
-    b = join_d(lo[1], hi[1]);
-}
-
-// every lane of each 16-lane row <- the sum over its row
-__device__ __forceinline__ double row_sum(double v)
-{
-    v += dpp_move<0xB1>(v);   // quad_perm [1,0,3,2]
-    v += dpp_move<0x4E>(v);   // quad_perm [2,3,0,1]
-    v += dpp_move<0x141>(v);  // row_half_mirror
-    v += dpp_move<0x140>(v);  // row_mirror
-    return v;
-}
+// Wave-wide sums in registers (no LDS traffic)
 
 template <int L>
 __device__ __forceinline__ double lane_value(double v)
@@ -425,19 +375,6 @@ __device__ __forceinline__ double lane_value(double v)
     const unsigned long long b = (unsigned long long)__double_as_longlong(v);
     return join_d((unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, L),
                   (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), L));
-}
-
-template <class F, int... J>
-__device__ __forceinline__ void static_for_impl(F &f, std::integer_sequence<int, J...>)
-{
-    (f(std::integral_constant<int, J>{}), ...);
-}
-
-// f(integral_constant<int, j>) for j = 0 .. n-1, in order
-template <int n, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    static_for_impl(f, std::make_integer_sequence<int, n>{});
 }
 
 // v[i] <- sum over the wave of v[i] for i < CNT, four sums at a time: the
@@ -473,11 +410,6 @@ __device__ __forceinline__ double wave_sum1(double v)
     double p = a + b, r = p;
     swap16(p, r);
     return row_sum(p + r);
-}
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
 // The same restarted GMRES with the Krylov basis in registers: unknown u of

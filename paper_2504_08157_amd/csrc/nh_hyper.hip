@@ -16,18 +16,9 @@
 // assembles the rows, wraps periodic directions and leaves taps past a wall
 // at zero.
 #include "nh_internal.h"
+#include "nh_lanes.h"
 
 namespace nh {
-
-// Workgroups are handed to the 8 XCDs round robin (b mod 8), each with its
-// own L2: give XCD x the contiguous range [x q + min(x, r), ...) of the n
-// logical blocks (q = n / 8, r = n mod 8), so that blocks running together on
-// one XCD cover neighbouring rows and their y taps hit that L2.
-__device__ __forceinline__ int hd_xcd_block(int b, int n)
-{
-    const int q = n >> 3, r = n & 7, x = b & 7, j = b >> 3;
-    return x * q + (x < r ? x : r) + j;
-}
 
 // out[f] = scale * L q[f] (out[f] += ... with ACC) for the 5 fields of
 // q [5][U].  Tiled column walk: a workgroup of 64 x 16 lattice columns of one
@@ -71,7 +62,7 @@ __global__ void __launch_bounds__(kHdTX * kHdTY) hd_laplace_tile_kernel(HyperPar
     const int nz = h.nz;
     const long U = nxy * nz;
     const int ntx = (h.nx + kHdTX - 1) / kHdTX, nty = (h.ny + kHdTY - 1) / kHdTY;
-    const int t = hd_xcd_block(blockIdx.x, gridDim.x);
+    const int t = xcd_block(blockIdx.x, gridDim.x);
     const int f = t / (ntx * nty), tt = t - f * ntx * nty;
     const int tx = threadIdx.x % kHdTX, ty = threadIdx.x / kHdTX;
     const int x0 = (tt % ntx) * kHdTX, y0 = (tt / ntx) * kHdTY;

@@ -17,9 +17,9 @@
 // optionally right-preconditioned by the column systems of the 1D split,
 // solved directly (the preconditioned vectors are kept, as flexible GMRES does).
 #include "nh_internal.h"
+#include "nh_lanes.h"
 
 #include <cmath>
-#include <utility>
 #include <vector>
 
 namespace nh {
@@ -44,12 +44,6 @@ namespace nh {
 // 256 x 256 x 41 nodes, N = 4: 55 us (85 before), 41 at the rate of a copy; the
 // residual form 96 us, where L and a combination with norms took 55 + 62.
 constexpr int kL3TX = 64, kL3TY = 8, kL3P = 1;
-
-__device__ __forceinline__ int l3_xcd_block(int b, int n)
-{
-    const int q = n >> 3, r = n & 7, x = b & 7, j = b >> 3;
-    return x * q + (x < r ? x : r) + j;
-}
 
 template <int I, int E, class F>
 __device__ __forceinline__ void l3_unrolled(F &&f)
@@ -80,7 +74,7 @@ __global__ void __launch_bounds__(kL3TX * kL3TY, N <= 4 ? 4 : 2) l3_tile_kernel(
     const int nz = h.nz;
     const long U = nxy * nz;
     const int ntx = (h.nx + kL3TX - 1) / kL3TX, nty = (h.ny + kL3TY - 1) / kL3TY;
-    const int t = l3_xcd_block(blockIdx.x, gridDim.x);
+    const int t = xcd_block(blockIdx.x, gridDim.x);
     const int tt = t % (ntx * nty), kc = t / (ntx * nty);
     const int kb = kc * kz, ke = kb + kz < nz ? kb + kz : nz;
     const int tx = threadIdx.x % kL3TX, ty = __builtin_amdgcn_readfirstlane(threadIdx.x / kL3TX);

@@ -28,6 +28,7 @@
 //     node.  HBM traffic per node and stage: read q^s (40 B), q^n (40 B, when
 //     used), forcing (16 B), write q^{s+1} (40 B).
 #include "nh_internal.h"
+#include "nh_lanes.h"
 
 #include <math.h>
 
@@ -513,20 +514,10 @@ __device__ __forceinline__ void stage_body(const StageParams &p, const int tile,
 #undef NH_PIN
 }
 
-// Workgroups are handed to the 8 XCDs round robin (b mod 8), and each XCD has
-// its own L2.  Give XCD x the contiguous tile range [x q + min(x, r), ...)
-// (q = n / 8, r = n mod 8): tiles that run at the same time on one XCD are
-// row neighbours whose x/y halos overlap, so halo re-reads hit that L2.
-__device__ __forceinline__ int xcd_tile(int b, int n)
-{
-    const int q = n >> 3, r = n & 7, x = b & 7, j = b >> 3;
-    return x * q + (x < r ? x : r) + j;
-}
-
 template <int N, int AX, int AY, typename T>
 __global__ void __launch_bounds__((StageShape<N, AX, AY>::NT)) stage_kernel(const StageParams p)
 {
-    stage_body<N, AX, AY, T>(p, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x);
+    stage_body<N, AX, AY, T>(p, xcd_block(blockIdx.x, gridDim.x), threadIdx.x);
 }
 
 // The same stage with each column cut into `nchunk` runs of elements, for
@@ -535,7 +526,7 @@ __global__ void __launch_bounds__((StageShape<N, AX, AY>::NT)) stage_kernel(cons
 template <int N, int AX, int AY, typename T>
 __global__ void __launch_bounds__((StageShape<N, AX, AY>::NT)) stage_kernel_split(const StageParams p, int nchunk)
 {
-    const int nt = p.ntx * p.nty, b = xcd_tile(blockIdx.x, gridDim.x);
+    const int nt = p.ntx * p.nty, b = xcd_block(blockIdx.x, gridDim.x);
     const int chunk = b / nt;
     stage_body<N, AX, AY, T, true>(p, b % nt, threadIdx.x, chunk * p.nelz / nchunk, (chunk + 1) * p.nelz / nchunk);
 }
@@ -1054,7 +1045,7 @@ __device__ __forceinline__ void stage_body_cls(const StageParams &p, const int t
 template <int N, int AX, int AY, typename T>
 __global__ void __launch_bounds__((ClsShape<N, AX, AY>::NT)) stage_kernel_cls(const StageParams p)
 {
-    stage_body_cls<N, AX, AY, T>(p, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x);
+    stage_body_cls<N, AX, AY, T>(p, xcd_block(blockIdx.x, gridDim.x), threadIdx.x);
 }
 
 template <int N, int AX, int AY, typename T>
