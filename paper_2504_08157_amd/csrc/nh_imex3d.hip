@@ -43,16 +43,7 @@ namespace nh {
 // level bases), and that the chunks spread evenly over the CUs (l3_levels).
 // 256 x 256 x 41 nodes, N = 4: 55 us (85 before), 41 at the rate of a copy; the
 // residual form 96 us, where L and a combination with norms took 55 + 62.
-constexpr int kL3TX = 64, kL3TY = 8, kL3P = 1;
-
-template <int I, int E, class F>
-__device__ __forceinline__ void l3_unrolled(F &&f)
-{
-    if constexpr (I < E) {
-        f(std::integral_constant<int, I>{});
-        l3_unrolled<I + 1, E>(f);
-    }
-}
+constexpr int kL3TX = 64, kL3TY = 8;
 
 // (lev and gz are h.lev and h.hv.gz passed again as restrict pointers so
 // that their per-level values are read with scalar loads)
@@ -68,7 +59,7 @@ __global__ void __launch_bounds__(kL3TX * kL3TY, N <= 4 ? 4 : 2) l3_tile_kernel(
     if (gate && *gate == 0) return;
     double norm2 = 0.0;
     constexpr int NC = 2 * N + 1, PX = kL3TX + 2 * N, PY = kL3TY + 2 * N, PS = PX * PY;
-    constexpr int NT = kL3TX * kL3TY, NH = (PS - NT + NT - 1) / NT, P = kL3P;   // NH: halo nodes per thread
+    constexpr int NT = kL3TX * kL3TY, NH = (PS - NT + NT - 1) / NT;   // NH: halo nodes per thread
     __shared__ double tile[2][3][PS];   // u, v, p'_L
     const long nxy = (long)h.nx * h.ny;
     const int nz = h.nz;
@@ -132,102 +123,99 @@ __global__ void __launch_bounds__(kL3TX * kL3TY, N <= 4 ? 4 : 2) l3_tile_kernel(
         const long L = (long)(kk < 0 ? 0 : kk < nz ? kk : nz - 1) * nxy;
         vert(kk, (x + L)[col], (x + 3 * U + L)[col], (x + 4 * U + L)[col], ta[o], tb[o]);
     }
-    // slot contents: rho', u, v, theta' of the halo nodes; all fields of the
+    // the next level's values: rho', u, v, theta' of the halo nodes; all fields of the
     // thread's node (rho', u, v, w, theta'); rho', w, theta' of its column at the
     // window's lead level (level + N)
-    double sr[P][NH], su[P][NH], sv2[P][NH], st[P][NH], ox[P][5], oz[P][3];
-    auto load = [&](int p, int k) {
+    double sr[NH], su[NH], sv2[NH], st[NH], ox[5], oz[3];
+    auto load = [&](int k) {
         const double *xl = x + level(k);
 #pragma unroll
         for (int i = 0; i < NH; ++i) {
-            sr[p][i] = xl[sc[i]];
-            su[p][i] = (xl + U)[sc[i]];
-            sv2[p][i] = (xl + 2 * U)[sc[i]];
-            st[p][i] = (xl + 4 * U)[sc[i]];
+            sr[i] = xl[sc[i]];
+            su[i] = (xl + U)[sc[i]];
+            sv2[i] = (xl + 2 * U)[sc[i]];
+            st[i] = (xl + 4 * U)[sc[i]];
         }
 #pragma unroll
-        for (int f = 0; f < 5; ++f) ox[p][f] = (xl + f * U)[cs];
-        const int kz = k + N;
-        const double *xz = x + (long)(kz < nz ? kz : nz - 1) * nxy;
-        oz[p][0] = xz[col];
-        oz[p][1] = (xz + 3 * U)[col];
-        oz[p][2] = (xz + 4 * U)[col];
+        for (int f = 0; f < 5; ++f) ox[f] = (xl + f * U)[cs];
+        const double *xz = x + (long)(k + N < nz ? k + N : nz - 1) * nxy;
+        oz[0] = xz[col];
+        oz[1] = (xz + 3 * U)[col];
+        oz[2] = (xz + 4 * U)[col];
     };
-    l3_unrolled<0, P>([&](auto J) { load(decltype(J)::value, kb + decltype(J)::value); });
-    for (int k0 = kb; k0 < ke; k0 += P) {
-        l3_unrolled<0, P>([&](auto J) {
-            constexpr int j = decltype(J)::value;
-            const int k = k0 + j;
-            const double *Lv = lev + (long)(k < ke ? k : ke - 1) * kLevW;
-            const double rho0 = Lv[0], p0 = Lv[2], dth0 = Lv[3], tau = Lv[4], irho0 = Lv[7], ith0 = Lv[8];
-            const double gp = gamma * p0;
-            double(*T)[PS] = tile[(k - kb) & 1];
+    // (written into the loop itself, a level spills registers: 62 us for 57 at 256 x 256 x 41)
+    auto step = [&](int k) {
+        const double *Lv = lev + (long)k * kLevW;
+        const double rho0 = Lv[0], p0 = Lv[2], dth0 = Lv[3], tau = Lv[4], irho0 = Lv[7], ith0 = Lv[8];
+        const double gp = gamma * p0;
+        double(*T)[PS] = tile[(k - kb) & 1];
 #pragma unroll
-            for (int i = 0; i < NH; ++i) {
-                if (si[i] >= 0) {
-                    T[0][si[i]] = sv[i] ? su[j][i] : 0.0;
-                    T[1][si[i]] = sv[i] ? sv2[j][i] : 0.0;
-                    T[2][si[i]] = sv[i] ? gp * (sr[j][i] * irho0 + st[j][i] * ith0) : 0.0;
+        for (int i = 0; i < NH; ++i) {
+            if (si[i] >= 0) {
+                T[0][si[i]] = sv[i] ? su[i] : 0.0;
+                T[1][si[i]] = sv[i] ? sv2[i] : 0.0;
+                T[2][si[i]] = sv[i] ? gp * (sr[i] * irho0 + st[i] * ith0) : 0.0;
+            }
+        }
+        const double xr = ox[0], xu = ox[1], xv = ox[2], xw = ox[3], xt = ox[4];
+        T[0][jo] = okc ? xu : 0.0;
+        T[1][jo] = okc ? xv : 0.0;
+        T[2][jo] = okc ? gp * (xr * irho0 + xt * ith0) : 0.0;
+        vert(k + N, oz[0], oz[1], oz[2], ta[2 * N], tb[2 * N]);
+        load(k + 1);
+        // vertical part at level k
+        const double *G = gz + (long)k * NC;
+        double d_rw = 0.0, d_pl = 0.0;
+#pragma unroll
+        for (int o = 0; o < NC; ++o) {
+            d_rw += G[o] * ta[o];
+            d_pl += G[o] * tb[o];
+        }
+#pragma unroll
+        for (int o = 0; o < 2 * N; ++o) {
+            ta[o] = ta[o + 1];
+            tb[o] = tb[o + 1];
+        }
+        __syncthreads();
+        double dux = 0.0, dpx = 0.0, dvy = 0.0, dpy = 0.0;
+#pragma unroll
+        for (int o = 0; o < NC; ++o) {
+            const int jx = (ty + N) * PX + tx + o, jy = (ty + o) * PX + tx + N;
+            dux += cx[o] * T[0][jx];
+            dpx += cx[o] * T[2][jx];
+            dvy += cy[o] * T[1][jy];
+            dpy += cy[o] * T[2][jy];
+        }
+        double Lr = -d_rw - rho0 * (dux + dvy);
+        double Lu = -irho0 * dpx, Lvv = -irho0 * dpy;
+        double Lw = -d_pl * irho0 - grav * xr * irho0 - tau * xw;
+        const double Lt = -xw * dth0;
+        if (!h.perx && (ix == 0 || ix == h.nx - 1)) Lu = 0.0;
+        if (!h.pery && (iy == 0 || iy == h.ny - 1)) Lvv = 0.0;
+        if (k == 0 || k == nz - 1) Lw = 0.0;
+        if (own) {
+            double *ol = out + (long)k * nxy;
+            if constexpr (RES) {
+                const double v[5] = {a * xr + c * Lr, a * xu + c * Lu, a * xv + c * Lvv, a * xw + c * Lw,
+                                     a * xt + c * Lt};
+                const double *bl = b + (long)k * nxy;
+#pragma unroll
+                for (int f = 0; f < 5; ++f) {
+                    const double r = (bl + f * U)[col] - v[f];
+                    norm2 += r * r;
+                    (ol + f * U)[col] = r;
                 }
+            } else {
+                ol[col] = a * xr + c * Lr;
+                (ol + U)[col] = a * xu + c * Lu;
+                (ol + 2 * U)[col] = a * xv + c * Lvv;
+                (ol + 3 * U)[col] = a * xw + c * Lw;
+                (ol + 4 * U)[col] = a * xt + c * Lt;
             }
-            const double xr = ox[j][0], xu = ox[j][1], xv = ox[j][2], xw = ox[j][3], xt = ox[j][4];
-            T[0][jo] = okc ? xu : 0.0;
-            T[1][jo] = okc ? xv : 0.0;
-            T[2][jo] = okc ? gp * (xr * irho0 + xt * ith0) : 0.0;
-            vert(k + N, oz[j][0], oz[j][1], oz[j][2], ta[2 * N], tb[2 * N]);
-            load(j, k + P);
-            // vertical part at level k
-            const double *G = gz + (long)(k < ke ? k : ke - 1) * NC;
-            double d_rw = 0.0, d_pl = 0.0;
-#pragma unroll
-            for (int o = 0; o < NC; ++o) {
-                d_rw += G[o] * ta[o];
-                d_pl += G[o] * tb[o];
-            }
-#pragma unroll
-            for (int o = 0; o < 2 * N; ++o) {
-                ta[o] = ta[o + 1];
-                tb[o] = tb[o + 1];
-            }
-            __syncthreads();
-            double dux = 0.0, dpx = 0.0, dvy = 0.0, dpy = 0.0;
-#pragma unroll
-            for (int o = 0; o < NC; ++o) {
-                const int jx = (ty + N) * PX + tx + o, jy = (ty + o) * PX + tx + N;
-                dux += cx[o] * T[0][jx];
-                dpx += cx[o] * T[2][jx];
-                dvy += cy[o] * T[1][jy];
-                dpy += cy[o] * T[2][jy];
-            }
-            double Lr = -d_rw - rho0 * (dux + dvy);
-            double Lu = -irho0 * dpx, Lvv = -irho0 * dpy;
-            double Lw = -d_pl * irho0 - grav * xr * irho0 - tau * xw;
-            const double Lt = -xw * dth0;
-            if (!h.perx && (ix == 0 || ix == h.nx - 1)) Lu = 0.0;
-            if (!h.pery && (iy == 0 || iy == h.ny - 1)) Lvv = 0.0;
-            if (k == 0 || k == nz - 1) Lw = 0.0;
-            if (own && k < ke) {
-                double *ol = out + (long)k * nxy;
-                if constexpr (RES) {
-                    const double v[5] = {a * xr + c * Lr, a * xu + c * Lu, a * xv + c * Lvv, a * xw + c * Lw,
-                                         a * xt + c * Lt};
-                    const double *bl = b + (long)k * nxy;
-#pragma unroll
-                    for (int f = 0; f < 5; ++f) {
-                        const double r = (bl + f * U)[col] - v[f];
-                        norm2 += r * r;
-                        (ol + f * U)[col] = r;
-                    }
-                } else {
-                    ol[col] = a * xr + c * Lr;
-                    (ol + U)[col] = a * xu + c * Lu;
-                    (ol + 2 * U)[col] = a * xv + c * Lvv;
-                    (ol + 3 * U)[col] = a * xw + c * Lw;
-                    (ol + 4 * U)[col] = a * xt + c * Lt;
-                }
-            }
-        });
-    }
+        }
+    };
+    load(kb);
+    for (int k = kb; k < ke; ++k) step(k);
     if constexpr (RES) {
         __shared__ double red[NT / 64];
 #pragma unroll
