@@ -582,17 +582,21 @@ struct Kry {
 //   M w = b_w - alpha (1/rho0) (D p_b + g b_rho),   p_b = gamma p0 (b_rho/rho0 + b_theta/theta0),
 //   rho' = b_rho - alpha D (rho0 w),   theta' = b_theta - alpha theta0' w
 // (D: the DSS'd vertical derivative; identity rows of M and unchanged w at the
-// walls).  pc_setup_kernel forms M from three stencil rows, inverts it (n_z <= 130:
-// in the LDS of one workgroup) and stores M^-1 and D as operands of
-// v_mfma_f64_16x16x4_f64, once per solve.  pc_apply_kernel then is three small
-// products per column, on the matrix cores: a wave holds 16 columns, column
-// lane % 16, and of block s of four levels the level 4 s + lane / 16.  That is the
-// B operand of k step s (k = lane / 16) and also the layout of the result (row
-// 4 i + lane / 16 in register i), so a product feeds the next without a shuffle
-// or LDS.
+// walls).  pc_setup_kernel forms M from three stencil rows, inverts it (n_z <= 130,
+// one workgroup) and stores M^-1 and D as operands of v_mfma_f64_16x16x4_f64, once
+// per solve.  pc_apply_kernel then is three small products per column, on the
+// matrix cores: a workgroup has 16 columns and a wave per 16-level tile of them; a
+// lane has column lane % 16 and of block s of four levels the level 4 s + lane / 16.
+// That is the B operand of k step s (k = lane / 16) and also the layout of the result
+// (row 4 i + lane / 16 in register i), so what the waves hand each other through LDS
+// is read and written without conflicts; a wave loads its operands of M^-1 ahead of
+// everything else.
 // Bound: the pass over memory, 5 fields read and 5 written (41 us for the 65536
 // columns of 41 levels of a 64 x 64 x 10, N = 4 mesh at the 5.15 TB/s of a copy;
-// 7 us of products): 48 us, where the column GMRES(10) to 1e-6 took 198.
+// 7 us of products): 47 us, where the column GMRES(10) to 1e-6 took 198.  With all
+// tiles of 16 columns in one wave, its registers full and every operand waited for:
+// 48 us there, and on 49, 77 and 129 levels of 36864 columns 75, 191 and 483 us
+// instead of 47, 71 and 138; of 256 columns 20, 33 and 76 instead of 7, 8 and 13.
 constexpr int kPcMaxTiles = 9;   // 16-level tiles: n_z <= 130 (and 144)
 
 __host__ __device__ constexpr int pc_halo(int N) { return (N + 3) / 4; }   // blocks of four levels beside a tile's own
@@ -608,20 +612,52 @@ static size_t pc_doubles(int nz, int N)
 size_t g3_precond_bytes(int nz, int N) { return nz <= 16 * kPcMaxTiles ? sizeof(double) * pc_doubles(nz, N) : 0; }
 
 constexpr int kPcThreads = 512;
+constexpr int kPcPanel = 8;   // columns per panel (16: 37 for 34 us at 41 levels, alike from 113 on, spills at 129)
 
-// M from the level table and the stencil rows (staged in LDS), then Gauss-Jordan
-// with partial pivoting in place: each step a pivot search by wave 0, then rank
-// one over the whole matrix; the column order is undone when the operands are
-// written.  83 us for 41 levels, once per step (its solves
-// share alpha).
+// lane l's value, l uniform
+__device__ __forceinline__ double lane_of(double v, int l)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    return join_d((unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l),
+                  (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l));
+}
+
+// every lane <- the largest of the wave
+__device__ __forceinline__ double wave_max(double v)
+{
+    v = fmax(v, lane_move<kSwapPair>(v));
+    v = fmax(v, lane_move<kSwapTwo>(v));
+    v = fmax(v, lane_move<kHalfMirror>(v));
+    v = fmax(v, lane_move<kRowMirror>(v));
+    double a = v, b = v;
+    swap16(a, b);
+    a = b = fmax(a, b);
+    swap32(a, b);
+    return fmax(a, b);
+}
+
+// M from the level table and the stencil rows (staged in LDS), then Gauss-Jordan in
+// place with partial pivoting, kPcPanel columns at a time.  The matrix stays in
+// registers as 16 x 16 tiles in the layout of an MFMA result, tile w + 8 m in wave w.
+// Per panel: its columns go through LDS to wave 0, which eliminates them in its own
+// registers (a lane has rows lane + 64 s; no barrier in the steps); then every other
+// element a_ij (0 in a pivot row) gains sum_m panel_im a_{p_m j}, two MFMAs a tile.  No rows
+// are exchanged: at the end row p_k stands for x_k and column k for right-hand side
+// p_k, and the operands are written accordingly.  Once per step (its solves share
+// alpha).  Bound: the chain of pivots, about 1 us each.  41, 77, 125 and 129 levels: 34, 72,
+// 144 and 191 us; the matrix in the LDS and a barrier after every search, row and
+// update: 83 us at 41 levels, about 1150 at 129.
+template <int NT>
 __global__ void __launch_bounds__(kPcThreads) pc_setup_kernel(HeviParams h, double alpha, double *__restrict__ pack)
 {
+    typedef double double4v __attribute__((ext_vector_type(4)));
+    constexpr int R = 16 * NT, PW = kPcPanel, W = kPcThreads / 64, MT = (NT * NT + W - 1) / W, NS = (R + 63) / 64;
     extern __shared__ double lds[];
-    const int n = h.nz, N = h.N, NC = 2 * N + 1, ld = n + 1, t = threadIdx.x;
-    const int lane = t % 64, wave = t / 64;
-    double *A = lds, *rowk = A + n * ld, *colk = rowk + n, *L0 = colk + n, *Lp = L0 + n, *L3 = Lp + n, *L7 = L3 + n,
-           *L8 = L7 + n, *G = L8 + n, *piv_l = G + n * NC;
-    int *pv = (int *)(piv_l + 1), *perm = pv + n;
+    __shared__ double panel[R][PW + 1], prow[PW][R + 1];
+    __shared__ int pv[R], kof[R], slot[R];   // p_k, its inverse, a row's place among the panel's pivots (-1: none)
+    const int n = h.nz, N = h.N, NC = 2 * N + 1, t = threadIdx.x, lane = t % 64, q = lane / 16, l16 = lane % 16;
+    const int wave = __builtin_amdgcn_readfirstlane(t / 64);
+    double *L0 = lds, *Lp = L0 + n, *L3 = Lp + n, *L7 = L3 + n, *L8 = L7 + n, *G = L8 + n;
     for (int k = t; k < n; k += kPcThreads) {
         const double *L = h.lev + (long)k * kLevW;
         L0[k] = L[0];
@@ -632,206 +668,265 @@ __global__ void __launch_bounds__(kPcThreads) pc_setup_kernel(HeviParams h, doub
     }
     for (int e = t; e < n * NC; e += kPcThreads) G[e] = h.gz[e];
     __syncthreads();
-    for (int i = wave; i < n; i += kPcThreads / 64)
-        for (int j = lane; j < n; j += 64) {
-            double m = i == j ? 1.0 : 0.0;
-            if (i > 0 && i < n - 1) {
-                // column j: rho'_k = -alpha D_kj rho0_j, theta'_j = -alpha theta0'_j
-                const double cj = -alpha * L0[j];
-                auto D = [&](int r, int c) { return c - r >= -N && c - r <= N ? G[r * NC + c - r + N] : 0.0; };
-                double dp = 0.0;
-                for (int k = i > N ? i - N : 0; k <= i + N && k < n; ++k) {
-                    double pk = cj * D(k, j) * L7[k];
-                    if (k == j) pk -= alpha * L3[j] * L8[k];
-                    dp += D(i, k) * Lp[k] * pk;
-                }
-                m += alpha * L7[i] * (dp + h.g * cj * D(i, j));
+    auto D = [&](int r, int c) { return c - r >= -N && c - r <= N ? G[r * NC + c - r + N] : 0.0; };
+    auto element = [&](int i, int j) {
+        double m = i == j && i < n ? 1.0 : 0.0;
+        if (i > 0 && i < n - 1 && j < n) {
+            // column j: rho'_k = -alpha D_kj rho0_j, theta'_j = -alpha theta0'_j
+            const double cj = -alpha * L0[j];
+            const int lo = i > j ? i - N : j - N, hi = i < j ? i + N : j + N;
+            double dp = 0.0;
+            for (int k = lo > 0 ? lo : 0; k <= hi && k < n; ++k) {
+                double pk = cj * D(k, j) * L7[k];
+                if (k == j) pk -= alpha * L3[j] * L8[k];
+                dp += D(i, k) * Lp[k] * pk;
             }
-            A[i * ld + j] = m;
+            m += alpha * L7[i] * (dp + h.g * cj * D(i, j));
         }
-    __syncthreads();
-    for (int k = 0; k < n; ++k) {
-        if (t < 64) {
-            double best = -1.0;
-            int bi = k;
-            for (int i = k + t; i < n; i += 64) {
-                const double v = fabs(A[i * ld + k]);
-                if (v > best) {
-                    best = v;
-                    bi = i;
-                }
-            }
+        return m;
+    };
+    // value i of tile (I, J): row 16 I + 4 i + lane / 16, column 16 J + lane % 16
+    double4v A[MT];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const double v = __shfl_xor(best, o);
-                const int vi = __shfl_xor(bi, o);
-                if (v > best || (v == best && vi < bi)) {
-                    best = v;
-                    bi = vi;
+    for (int m = 0; m < MT; ++m) {
+        const int id = wave + W * m, I = id / NT, J = id % NT;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) A[m][i] = id < NT * NT ? element(16 * I + 4 * i + q, 16 * J + l16) : 0.0;
+    }
+    unsigned taken = 0;   // wave 0, bit s: row lane + 64 s has been a pivot row
+    for (int c0 = 0; c0 < n; c0 += PW) {
+        const int nk = n - c0 < PW ? n - c0 : PW;
+        const bool mine = l16 / PW == c0 % 16 / PW;   // the lane's column in the panel's tiles is one of the panel
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const int id = wave + W * m, I = id / NT;
+            if (id < NT * NT && id % NT == c0 / 16 && mine)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) panel[16 * I + 4 * i + q][l16 % PW] = A[m][i];
+        }
+        for (int i = t; i < R; i += kPcThreads) slot[i] = -1;
+        for (int e = t; e < PW * R; e += kPcThreads) prow[e / R][e % R] = 0.0;
+        __syncthreads();
+        if (wave == 0) {
+            double X[NS][PW];
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int c = 0; c < PW; ++c) X[s][c] = lane + 64 * s < R ? panel[lane + 64 * s][c] : 0.0;
+            static_for<PW>([&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value;
+                if (j < nk) {
+                    // a NaN counts less than any number and more than a row taken
+                    double v[NS], iv[NS], m = -1.0;
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        const double x = fabs(X[s][j]);
+                        v[s] = lane + 64 * s < n && !(taken >> s & 1) ? (x >= 0.0 ? x : -0.5) : -1.0;
+                        iv[s] = 1.0 / X[s][j];
+                        m = fmax(m, v[s]);
+                    }
+                    m = wave_max(m);
+                    int sp = -1, lp = 0;
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        const unsigned long long w = __ballot(v[s] == m);
+                        if (sp < 0 && w) {
+                            sp = s;
+                            lp = __builtin_ctzll(w);
+                        }
+                    }
+                    // the pivot row, scaled
+                    double r[PW];
+                    static_for<NS>([&](auto sc) __attribute__((always_inline)) {
+                        constexpr int s = decltype(sc)::value;
+                        if (sp == s) {
+                            const double ip = lane_of(iv[s], lp);
+#pragma unroll
+                            for (int c = 0; c < PW; ++c) r[c] = c == j ? ip : lane_of(X[s][c], lp) * ip;
+                        }
+                    });
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        const double f = X[s][j];
+#pragma unroll
+                        for (int c = 0; c < PW; ++c) X[s][c] = (c == j ? 0.0 : X[s][c]) - f * r[c];
+                    }
+                    static_for<NS>([&](auto sc) __attribute__((always_inline)) {
+                        constexpr int s = decltype(sc)::value;
+                        if (sp == s && lane == lp) {
+#pragma unroll
+                            for (int c = 0; c < PW; ++c) X[s][c] = r[c];
+                            taken |= 1u << s;
+                            slot[64 * s + lp] = j;
+                            pv[c0 + j] = 64 * s + lp;
+                            kof[64 * s + lp] = c0 + j;
+                        }
+                    });
                 }
-            }
-            if (t == 0) {
-                pv[k] = bi;
-                *piv_l = 1.0 / A[bi * ld + k];
-            }
+            });
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int c = 0; c < PW; ++c)
+                    if (lane + 64 * s < R) panel[lane + 64 * s][c] = X[s][c];
         }
         __syncthreads();
-        const int p = pv[k];
-        const double ip = *piv_l;
-        // the pivot row out, row k in its place (only row p is written), and column k
-        for (int j = t; j < n; j += kPcThreads) {
-            colk[j] = A[(j == p ? k : j) * ld + k];
-            const double r = A[p * ld + j];
-            A[p * ld + j] = A[k * ld + j];
-            rowk[j] = j == k ? ip : r * ip;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const int id = wave + W * m, I = id / NT, J = id % NT;
+            if (id < NT * NT)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int p = slot[16 * I + 4 * i + q];
+                    if (p >= 0) {
+                        prow[p][16 * J + l16] = A[m][i];
+                        A[m][i] = 0.0;
+                    }
+                }
         }
         __syncthreads();
-        for (int j = lane; j < n; j += 64) {
-            const double r = rowk[j];
-            for (int i = wave; i < n; i += kPcThreads / 64)
-                A[i * ld + j] = i == k ? r : (j == k ? 0.0 : A[i * ld + j]) - colk[i] * r;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const int id = wave + W * m, I = id / NT, J = id % NT;
+            if (id < NT * NT) {
+#pragma unroll
+                for (int k = 0; k < PW; k += 4)
+                    A[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(panel[16 * I + l16][k + q], prow[k + q][16 * J + l16], A[m],
+                                                                0, 0, 0);
+                if (J == c0 / 16 && mine)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) A[m][i] = panel[16 * I + 4 * i + q][l16 % PW];
+            }
         }
         __syncthreads();
     }
-    for (int j = t; j < n; j += kPcThreads) {   // the exchanges of columns, last first
-        int c = j;
-        for (int k = 0; k < n; ++k) c = c == k ? pv[k] : c == pv[k] ? k : c;
-        perm[j] = c;
-    }
-    __syncthreads();
-    const int NT = (n + 15) / 16, S = 4 * NT, HB = (N + 3) / 4, NB = pc_band(HB);
-    for (int e = t; e < NT * S * 64; e += kPcThreads) {
-        const int l = e % 64, s = e / 64 % S, T = e / (64 * S);
-        const int i = 16 * T + l % 16, k = 4 * s + l / 16;
-        pack[e] = i < n && k < n ? A[i * ld + perm[k]] : 0.0;
+    constexpr int S = 4 * NT;
+    const int HB = pc_halo(N), NBD = pc_band(HB);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        const int id = wave + W * m;
+        if (id < NT * NT)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = 16 * (id / NT) + 4 * i + q, c = 16 * (id % NT) + l16;
+                const bool in = r < n && c < n;
+                const int x = in ? kof[r] : r, k = in ? pv[c] : c;
+                pack[((long)(x / 16) * S + k / 4) * 64 + k % 4 * 16 + x % 16] = in ? A[m][i] : 0.0;
+            }
     }
     double *pd = pack + (long)NT * S * 64;
-    for (int e = t; e < NT * NB * 64; e += kPcThreads) {
-        const int l = e % 64, b = e / 64 % NB, T = e / (64 * NB);
+    for (int e = t; e < NT * NBD * 64; e += kPcThreads) {
+        const int l = e % 64, b = e / 64 % NBD, T = e / (64 * NBD);
         const int i = 16 * T + l % 16, k = 4 * (4 * T - HB + b) + l / 16;
         pd[e] = i < n && k >= 0 && k < n && k - i >= -N && k - i <= N ? G[i * NC + k - i + N] : 0.0;
     }
 }
 
 template <int NT, int HB>
-__global__ void __launch_bounds__(256) pc_apply_kernel(HeviParams h, double alpha, const double *__restrict__ v,
-                                                       double *__restrict__ z, const double *__restrict__ pack,
-                                                       const double *__restrict__ lev, const int *gate,
-                                                       const double *scale)
+__global__ void __launch_bounds__(64 * NT) pc_apply_kernel(HeviParams h, double alpha,
+                                                                const double *__restrict__ v, double *__restrict__ z,
+                                                                const double *__restrict__ pack,
+                                                                const double *__restrict__ lev, const int *gate,
+                                                                const double *scale)
 {
     if (gate && *gate == 0) return;
-    const double sc = scale ? *scale : 1.0;
     typedef double double4v __attribute__((ext_vector_type(4)));
     constexpr int S = 4 * NT, NB = pc_band(HB);
-    const int lane = threadIdx.x % 64, q = lane / 16;
-    const long nxy = (long)h.nx * h.ny, U = nxy * h.nz;
-    const long c0 = (blockIdx.x * 4L + threadIdx.x / 64) * 16;
-    if (c0 >= nxy) return;
-    const long c = c0 + lane % 16;
+    __shared__ double su[S][64], sw[S][64];
+    const double sc = scale ? *scale : 1.0;
+    const int lane = threadIdx.x % 64, T = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), q = lane / 16;
+    const long nxy = (long)h.nx * h.ny, U = nxy * h.nz, c = blockIdx.x * 16L + lane % 16;
     const bool own = c < nxy;
     const double *x = v + (own ? c : nxy - 1);
     double *y = z + c;
     const int nz = h.nz;
-    // u and v with the other loads where registers allow, else at the end
-    constexpr bool kUvFirst = NT <= 4;
-    double br[S], bw[S], bt[S], bu[kUvFirst ? S : 1], bv[kUvFirst ? S : 1];
+    const double *pm = pack + (long)T * S * 64 + lane, *pd = pack + ((long)NT * S + T * NB) * 64 + lane;
+    double om[S], od[NB], br[4], bw[4], bt[4], bu[4], bv[4], L0[4], L3[4], L7[4];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        const int k = 4 * s + q;
+    for (int i = 0; i < 4; ++i) {
+        const int k = 4 * (4 * T + i) + q;
         const long o = (long)(k < nz ? k : nz - 1) * nxy;
-        br[s] = sc * x[o];
-        if constexpr (kUvFirst) {
-            bu[s] = sc * x[U + o];
-            bv[s] = sc * x[2 * U + o];
-        }
-        bw[s] = sc * x[3 * U + o];
-        bt[s] = sc * x[4 * U + o];
+        br[i] = sc * x[o];
+        bu[i] = sc * x[U + o];
+        bv[i] = sc * x[2 * U + o];
+        bw[i] = sc * x[3 * U + o];
+        bt[i] = sc * x[4 * U + o];
     }
-    const double *pm = pack + lane, *pd = pack + (long)NT * S * 64 + lane;
-    // acc = D u over the levels of tile T
-    auto deriv = [&](int T, const double (&u)[S]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) od[b] = pd[b * 64];
+#pragma unroll
+    for (int s = 0; s < S; ++s) om[s] = pm[s * 64];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = 4 * (4 * T + i) + q;
+        const bool in = k < nz;
+        const double *L = lev + (long)(in ? k : nz - 1) * kLevW;
+        L0[i] = L[0];
+        L3[i] = L[3];
+        L7[i] = L[7];
+        su[4 * T + i][lane] = in ? h.gamma * L[2] * (br[i] * L[7] + bt[i] * L[8]) : 0.0;
+        if (own && in) {
+            const long o = (long)k * nxy;
+            y[U + o] = bu[i];
+            y[2 * U + o] = bv[i];
+        }
+    }
+    // D u over the levels of the tile
+    auto deriv = [&]() __attribute__((always_inline)) {
         double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int s = 4 * T - HB + b;
-            if (s >= 0 && s < S) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pd[(T * NB + b) * 64], u[s], acc, 0, 0, 0);
+            if (s >= 0 && s < S) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(od[b], su[s][lane], acc, 0, 0, 0);
         }
         return acc;
     };
-    double u[S];   // p_b, then rho0 w
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        const int k = 4 * s + q;
-        const bool in = k < nz;
-        const double *L = lev + (long)(in ? k : nz - 1) * kLevW;
-        u[s] = in ? h.gamma * L[2] * (br[s] * L[7] + bt[s] * L[8]) : 0.0;
-        if constexpr (kUvFirst)
-            if (own && in) {
-                const long o = (long)k * nxy;
-                y[U + o] = bu[s];
-                y[2 * U + o] = bv[s];
-            }
-    }
-    double w[S];   // right-hand sides
-#pragma unroll
-    for (int T = 0; T < NT; ++T) {
-        const double4v acc = deriv(T, u);
+    __syncthreads();
+    {
+        const double4v acc = deriv();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int s = 4 * T + i, k = 4 * s + q;
-            const double L7 = lev[(long)(k < nz ? k : nz - 1) * kLevW + 7];
-            const double r = k > 0 && k < nz - 1 ? bw[s] - alpha * L7 * (acc[i] + h.g * br[s]) : bw[s];
-            w[s] = k < nz ? r : 0.0;
+            const int k = 4 * (4 * T + i) + q;
+            const double r = k > 0 && k < nz - 1 ? bw[i] - alpha * L7[i] * (acc[i] + h.g * br[i]) : bw[i];
+            sw[4 * T + i][lane] = k < nz ? r : 0.0;
         }
     }
-#pragma unroll
-    for (int T = 0; T < NT; ++T) {
+    __syncthreads();
+    {
         double4v acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int s = 0; s < S; ++s)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pm[(T * S + s) * 64], w[s], acc, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bw[4 * T + i] = acc[i];
-    }
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        const int k = 4 * s + q;
-        const bool in = k < nz;
-        const double *L = lev + (long)(in ? k : nz - 1) * kLevW;
-        u[s] = in ? L[0] * bw[s] : 0.0;
-        if (own && in) {
-            const long o = (long)k * nxy;
-            y[3 * U + o] = bw[s];
-            y[4 * U + o] = bt[s] - alpha * L[3] * bw[s];
-        }
-    }
-#pragma unroll
-    for (int T = 0; T < NT; ++T) {
-        const double4v acc = deriv(T, u);
+        for (int s = 0; s < S; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(om[s], sw[s][lane], acc, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int s = 4 * T + i, k = 4 * s + q;
-            if (own && k < nz) y[(long)k * nxy] = br[s] - alpha * acc[i];
-        }
-    }
-    if constexpr (!kUvFirst) {
-#pragma unroll 8
-        for (int s = 0; s < S; ++s) {
-            const int k = 4 * s + q;
+            const int k = 4 * (4 * T + i) + q;
+            su[4 * T + i][lane] = k < nz ? L0[i] * acc[i] : 0.0;
             if (own && k < nz) {
                 const long o = (long)k * nxy;
-                y[U + o] = sc * x[U + o];
-                y[2 * U + o] = sc * x[2 * U + o];
+                y[3 * U + o] = acc[i];
+                y[4 * U + o] = bt[i] - alpha * L3[i] * acc[i];
             }
         }
+    }
+    __syncthreads();
+    const double4v acc = deriv();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = 4 * (4 * T + i) + q;
+        if (own && k < nz) y[(long)k * nxy] = br[i] - alpha * acc[i];
     }
 }
 
-static hipError_t launch_pc_setup(const L3Params &h, double alpha, double *pack, hipStream_t s)
+template <int NT>
+static hipError_t launch_pc_setup(int nt, const L3Params &h, double alpha, double *pack, hipStream_t s)
 {
-    const size_t n = h.nz, lds = sizeof(double) * (n * (n + 1) + 7 * n + n * (2 * h.N + 1) + 1) + sizeof(int) * 2 * n;
-    hipLaunchKernelGGL(pc_setup_kernel, dim3(1), dim3(kPcThreads), lds, s, h.hv, alpha, pack);
-    return hipGetLastError();
+    if constexpr (NT > kPcMaxTiles) {
+        return hipErrorInvalidValue;
+    } else {
+        if (nt != NT) return launch_pc_setup<NT + 1>(nt, h, alpha, pack, s);
+        const size_t lds = sizeof(double) * (size_t)h.nz * (5 + 2 * h.N + 1);
+        hipLaunchKernelGGL((pc_setup_kernel<NT>), dim3(1), dim3(kPcThreads), lds, s, h.hv, alpha, pack);
+        return hipGetLastError();
+    }
 }
 
 template <int NT>
@@ -842,13 +937,11 @@ static hipError_t launch_pc_apply(int nt, const L3Params &h, double alpha, const
         return hipErrorInvalidValue;
     } else {
         if (nt != NT) return launch_pc_apply<NT + 1>(nt, h, alpha, v, z, pack, gate, scale, s);
-        const dim3 grid((unsigned)(((long)h.nx * h.ny + 63) / 64)), blk(256);
+        const dim3 grid((unsigned)(((long)h.nx * h.ny + 15) / 16)), blk(64 * NT);
         if (pc_halo(h.N) == 1)
-            hipLaunchKernelGGL((pc_apply_kernel<NT, 1>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate,
-                               scale);
+            hipLaunchKernelGGL((pc_apply_kernel<NT, 1>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate, scale);
         else
-            hipLaunchKernelGGL((pc_apply_kernel<NT, 2>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate,
-                               scale);
+            hipLaunchKernelGGL((pc_apply_kernel<NT, 2>), grid, blk, 0, s, h.hv, alpha, v, z, pack, h.lev, gate, scale);
         return hipGetLastError();
     }
 }
@@ -869,7 +962,7 @@ hipError_t gmres3d(const L3Params &h, const G3Work &w, double alpha, const doubl
     double *V = w.V;   // (m + 1) vectors of n
     *iters = 0;
     *relres = 0.0;
-    if (precond && !pc_ready && (e = launch_pc_setup(h, alpha, w.pc, s)) != hipSuccess) return e;
+    if (precond && !pc_ready && (e = launch_pc_setup<1>((h.nz + 15) / 16, h, alpha, w.pc, s)) != hipSuccess) return e;
     // ||b||; the first cycle starts from x0 (or b) and writes x; x = 0 when b = 0
     k.dots(V, 0, b, nullptr);
     hipLaunchKernelGGL(g3_begin_kernel, dim3(1), dim3(kKryCtl), 0, s, st, (const double *)w.part, w.status_dev);
