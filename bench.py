@@ -939,6 +939,7 @@ def main():
             "dof_convention": "unique nodes x 5 fields; paper convention (E (N+1)^3 x 5) = "
                               f"{value * ctx.L / U:.4e}",
             "dt": dt, "precision": args.precision,
+            # both workloads have a tile for every CU: variant 0 runs whole columns of this tile on them
             "tile_variant": tile, "tile_columns": list(nhsem.nh_tile_shape(w.mesh.order, tile)),
             "tile_ms_per_step": {str(k): v for k, v in tune.items()},
             "parallelism": "single GPU",

@@ -100,18 +100,22 @@ nh_status nh_set_stream(nh_ctx *ctx, void *hip_stream);
 /* Switch element arithmetic between NH_FP64 and NH_FP32_MIXED. */
 nh_status nh_set_precision(nh_ctx *ctx, int32_t precision);
 
-/* Workgroup tile of the stage kernel (columns per workgroup from
-   nh_tile_shape): variant 0 (default) rows of ~32 lattice columns, a few
-   element rows deep; variant 1 a squarer ~16 x 16 tile.  Variants 0 and 1
-   compute every node with the same arithmetic in the same order, so results
-   are bitwise identical.  Variant 2 (order 4 only; other orders run variant
-   0) is variant 0's tile with the nodes assigned to threads by node class and
-   the x/y derivatives written per element (a different order of the same
-   sums: equal to variants 0 and 1 to rounding).  Chosen by the caller's tuner
-   from measured times.  NH_EINVAL for any other value. */
+/* Workgroup tile of the stage kernel: variant 0 (default) rows of ~32 lattice
+   columns, a few element rows deep; variant 1 a squarer ~16 x 16 tile.  With
+   variant 0 a single context takes that tile with whole columns, or, on
+   lattices with too few tiles for the chip, one of four shapes with the
+   columns cut into runs of elements, chosen from order and lattice when the
+   context is made (a batch always takes the variants' own tiles).  All of
+   these compute every node with the same arithmetic in the same order, so
+   results are bitwise identical.  Variant 2: at order 4 variant 0's tile with
+   the nodes assigned to threads by node class and the x/y derivatives written
+   per element (a different order of the same sums: equal to variants 0 and 1
+   to rounding), at other orders a third tile shape.  Chosen by the caller's
+   tuner from measured times.  NH_EINVAL for any other value. */
 nh_status nh_set_tile(nh_ctx *ctx, int32_t variant);
 
-/* Columns per tile (tx x ty) of a variant for order N (no context needed). */
+/* Columns per tile (tx x ty) of a variant for order N (no context needed);
+   of variant 0 the tile of whole columns, whatever a context runs. */
 nh_status nh_tile_shape(int32_t order, int32_t variant, int32_t *tx, int32_t *ty);
 
 /* Sizes: U unique nodes, L local nodes (E (N+1)^3), lattice n[3]. */

@@ -23,9 +23,9 @@
 //
 // What bounds it: VALU issue of one wave per SIMD (the basis fills the
 // register file).  Measured on 147,456 columns of 16 order-4 elements
-// (n_z = 65, GMRES(10) to 1e-10, 27 steps): 2.63 ms per solve against 6.88
-// with one column per wave, 225 VALU instructions per column and step
-// against 524, VALU active 59 % of the cycles.
+// (n_z = 65, GMRES(10) to 1e-10, 28.9 steps): 3.23 ms per solve against 7.53
+// with one column per wave, 234 VALU instructions per column and step
+// against 524, VALU issue in 51 % of the cycles.
 #include "nh_internal.h"
 #include "nh_lanes.h"
 
@@ -736,8 +736,8 @@ gmres_elem_kernel(const HeviParams h, const GmresArgs g, const int ngrp)
 
 // Schur form, four columns per wave, restart length M.  N unknowns per lane,
 // so the basis leaves room for two waves per SIMD (orders above 4: one).
-// Measured as the preconditioner of a 3D-IMEX step (65,536 columns, n_z = 41,
-// to 1e-6): 0.197 ms per solve against 0.592 with one column per wave.
+// Measured on the 147,456 columns above (14.6 steps): 0.76 ms per solve against
+// 3.17 with one column per wave.
 template <int N, bool FULL, int M>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(N <= 4 ? 2 : 1, N <= 4 ? 2 : 1)))
 gmres_schur_elem_kernel(const HeviParams h, const GmresArgs g, const int ngrp)
@@ -843,9 +843,12 @@ gmres_schur_elem_kernel(const HeviParams h, const GmresArgs g, const int ngrp)
 // rows need d(rho0 w)/dz, w rows dp'_L/dz).  The top level is level 0 of
 // lanes 2 nelz + f when nelz < 16; with 16 elements (FULL) one extra slot holds
 // it: theta' in lane 29, w in lane 30, rho' in lane 31.  Measured at restart 20
-// (17,760 columns, n_z = 49, 40 steps): 1.52 ms per solve against 7.18 with
+// (17,760 columns, n_z = 49, 40 steps): 1.25 ms per solve against 7.18 with
 // one column per wave and the basis in LDS; at restart 10 the one-lane form
-// is faster (2.63 ms against 3.55 on the 147,456 columns above).
+// was the faster one of the two (2.63 ms against 3.55 on 147,456 columns).
+// Bound: the latency of its own chain in one wave per SIMD (36 KB of LDS hold the
+// six other vectors: four waves to a CU, so those columns are 8.7 rounds of waves):
+// VALU active in 52 % of the wave's cycles, 2 % wait to issue, under 1 % for LDS.
 template <int N>
 struct HalfCf {   // a lane's coefficients
     static constexpr int H = (N + 1) / 2;
@@ -1053,9 +1056,10 @@ template <int N, bool FULL>
 void launch_forms(const HeviParams &h, const GmresArgs &g, hipStream_t s)
 {
     // basis vectors kept in registers at order N (the rest in LDS): the most
-    // that fit 512 registers without scratch; of the 20 of the half form, 14
-    // and 16 measured alike (3.41 ms per HEVI step), 12 and 10 slower (4.7:
-    // their LDS vectors leave three waves per CU instead of four)
+    // that fit 512 registers without scratch; of the 20 of the half form 14
+    // (orders 5 and 6 then spill 76 to 236 bytes a lane): 14 and 16 measured
+    // alike at order 4 (3.41 ms per HEVI step, 2.84 now), 12 and 10 slower
+    // (4.7: their LDS vectors leave three waves per CU instead of four)
     constexpr int VR = N <= 4 ? kGmresRegM : N == 5 ? 8 : 6;
     constexpr int VRH = 14;
     const long ncol = (long)h.nx * h.ny;

@@ -595,7 +595,7 @@ struct Kry {
 // columns of 41 levels of a 64 x 64 x 10, N = 4 mesh at the 5.15 TB/s of a copy;
 // 7 us of products): 47 us, where the column GMRES(10) to 1e-6 took 198.  With all
 // tiles of 16 columns in one wave, its registers full and every operand waited for:
-// 48 us there, and on 49, 77 and 129 levels of 36864 columns 75, 191 and 483 us
+// 48 us there, and on 61, 77 and 129 levels of 36864 columns 75, 191 and 483 us
 // instead of 47, 71 and 138; of 256 columns 20, 33 and 76 instead of 7, 8 and 13.
 constexpr int kPcMaxTiles = 9;   // 16-level tiles: n_z <= 130 (and 144)
 

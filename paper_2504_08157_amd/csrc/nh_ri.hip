@@ -101,7 +101,7 @@ __device__ __forceinline__ void ri_chunk(const RiParams &p, int b, B &&begin, R 
 
 // s0 = sum m |u|, s1 = sum m |u| x, s2 = sum m |u| y over chunk b of level k
 // (m = m_x m_y, the level's 2D quadrature weight up to the level's factor).
-// Bound: the three fields it reads (512 x 512 x 81 nodes: 98 us, 5.2 TB/s; 122 with
+// Bound: the three fields it reads (512 x 512 x 81 nodes: 93 us, 5.5 TB/s; 122 with
 // an index divided for every node).
 __global__ void __launch_bounds__(kRiThreads) ri_centroid_partial(RiParams p, const double *__restrict__ q,
                                                                    double *__restrict__ part)
@@ -214,7 +214,7 @@ __device__ __forceinline__ double ri_quotient(double c, double s, double y)
 // strip sums and counts of chunk b of level k, and its maximum horizontal
 // speed.  The levels go from the last to the first: the centroid pass leaves the
 // last ones in the Infinity Cache (10 us of a call).  Bound: FP64 arithmetic and
-// the LDS additions.  512 x 512 x 81 nodes, 50 strips: 103 us (152 with a division and
+// the LDS additions.  512 x 512 x 81 nodes, 50 strips: 111 us (152 with a division and
 // a root per node, divided indices and an LDS addition per node).
 __global__ void __launch_bounds__(kRiThreads) ri_strip_partial(RiParams p, const double *__restrict__ q,
                                                                 const double *__restrict__ center,
@@ -316,7 +316,7 @@ __device__ __forceinline__ void ri_block_best(double &v, long &at, double *rv, l
 // strip means of level k = blockIdx.x from its nb partials, the largest of
 // them and the largest speed of the level into lev[3 k ..] (value, strip or -1,
 // speed).  The partials of a strip are summed in parts by threads of their own
-// (the parts then in order): 512 x 512 x 81 nodes, 50 strips: 13 us and 4 for the
+// (the parts then in order): 512 x 512 x 81 nodes, 50 strips: 13 us and 5 for the
 // last kernel (27 and 18 with one thread per strip and one workgroup for the maxima).
 __global__ void __launch_bounds__(kRiThreads) ri_strip_final(RiParams p, const double *__restrict__ ssum,
                                                               const int *__restrict__ scnt,
