@@ -1295,13 +1295,14 @@ static void launch_split(int N, int precision, int shape, const StageParams &p, 
 // column that waits for a CU 5.5) and a launch 3 us, the elements take up to
 // 15 % longer as the chip fills, and small workgroups that share a CU finish in
 // 0.8 of their time alone.  A plan other than whole columns of shape 0 is taken
-// where it gains 10 % or more (order 2, whose short elements the estimate
-// prices too high, 16 %): the 512 x 512 x 81 and 256 x 256 x 41 lattices (1024 and
-// 256 tiles) keep them.  FP32-mixed takes the same plan: its elements are faster
-// by about the same share in every shape.  Over 230 lattices, against whole
-// columns of shape 0: geometric mean 2.04x in FP64 and 1.94x in FP32-mixed (the
-// best plan of each 2.06x and 1.98x), the worst 0.97x; with 3.5 us throughout and
-// 6 % 2.04x and 1.93x, the worst 0.90x and 0.85x.  Over 260 others 1.99x and 1.90x.
+// where it gains 10 % or more (columns of one element, with no chain to add up,
+// 8 %; order 2, whose short elements the estimate prices too high, 16 %): the
+// 512 x 512 x 81 and 256 x 256 x 41 lattices (1024 and 256 tiles) keep them.
+// FP32-mixed takes the same plan: its elements are faster by about the same
+// share in every shape.  Over 230 lattices, against whole columns of shape 0:
+// geometric mean 2.04x in FP64 and 1.94x in FP32-mixed (the best plan of each
+// 2.06x and 1.98x), the worst 0.97x; with 3.5 us throughout and 6 % 2.04x and
+// 1.93x, the worst 0.90x and 0.85x.  Over 150 others 2.24x and 2.12x, none slower.
 void stage_plan(int N, int nx, int ny, int nelz, int *shape, int *nchunk)
 {
     static const double tau[5][4] = {{3.2, 3.7, 4.5, 3.0}, {5.7, 6.1, 6.1, 3.8}, {6.0, 7.3, 4.9, 4.6},
@@ -1331,7 +1332,7 @@ void stage_plan(int N, int nx, int ny, int nelz, int *shape, int *nchunk)
                 t = one * (double)((long)((n + 255.0) / 256.0));
             }
             t += 3.0;
-            if (s == 0 && z == 1) best = (N == 2 ? 0.84 : 0.9) * t;
+            if (s == 0 && z == 1) best = (N == 2 ? 0.84 : nelz == 1 ? 0.92 : 0.9) * t;
             else if (t < best) {
                 best = t;
                 *shape = s;
