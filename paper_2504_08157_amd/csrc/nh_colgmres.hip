@@ -29,6 +29,7 @@
 #include "nh_internal.h"
 #include "nh_lanes.h"
 
+#include <float.h>
 #include <math.h>
 
 namespace nh {
@@ -804,8 +805,11 @@ gmres_schur_elem_kernel(const HeviParams h, const GmresArgs g, const int ngrp)
                     for (int l = 0; l < N; ++l) sx[l][lane] = xd[l];
             }
         }
-        gmres_lanes<Row16, Op, M, M>(op, beta, g.rtol * bn, g.restart, g.max_restarts, act, sx, sb, nullptr, sH[row],
-                                     conv, iters);
+        // finite (or NaN): a right-hand side with an infinity has an infinite
+        // residual, which must not pass for a solution
+        const double tol = g.rtol * bn > DBL_MAX ? DBL_MAX : g.rtol * bn;
+        gmres_lanes<Row16, Op, M, M>(op, beta, tol, g.restart, g.max_restarts, act, sx, sb, nullptr, sH[row], conv,
+                                     iters);
         asm volatile("" : "+v"(el));
         // rho' and theta' from the full w column
         load_b();

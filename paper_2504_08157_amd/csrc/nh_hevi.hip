@@ -26,6 +26,7 @@
 #include "nh_internal.h"
 #include "nh_lanes.h"
 
+#include <float.h>
 #include <math.h>
 
 namespace nh {
@@ -834,7 +835,9 @@ __global__ void __launch_bounds__(64) gmres_schur_kernel(HeviParams h, GmresArgs
             bn2 += a * a + w * w + t * t;
         }
         const double bn = sqrt(wave_sum1(bn2));
-        const double tol = g.rtol * bn;
+        // finite (or NaN): a right-hand side with an infinity has an infinite
+        // residual, which must not pass for a solution
+        const double tol = g.rtol * bn > DBL_MAX ? DBL_MAX : g.rtol * bn;
         // reduced right-hand side: b_w + alpha L_w(b_rho + alpha L_rw w_wall, b_th + alpha L_tw w_wall)
         for (int k = lane; k < nz; k += 64) ww[k] = (k == 0 || k == nz - 1) ? bw[k] : 0.0;
         wave_sync();
