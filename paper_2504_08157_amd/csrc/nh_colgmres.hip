@@ -361,7 +361,7 @@ __device__ __forceinline__ void gmres_lanes(const Op &op, double al, double tol,
             if (run) {
                 ++iters;
                 jn = j + 1;
-                est = nn2 <= 0.0 || rt2 <= pp;
+                est = (Op::NAN_ENDS ? brk : nn2 <= 0.0) || rt2 <= pp;
                 run = !est;
             }
         }
@@ -496,6 +496,7 @@ template <int N, bool FULL>
 struct ElemOp {
     using C = Cf<N>;
     static constexpr int S = 3 * N + (FULL ? 1 : 0), NC = C::COUNT, TDL = kColElems - 3;
+    static constexpr bool NAN_ENDS = false;   // a NaN ends a cycle of GMRES
     const double (*sc)[kColElems];
     DMat<N> D;
     double grav;
@@ -552,6 +553,7 @@ template <int N, bool FULL>
 struct SchurOp {
     using C = Cf<N>;
     static constexpr int S = N, NC = C::COUNT, TDL = kColElems - 1;
+    static constexpr bool NAN_ENDS = true;
     const double (*sc)[kColElems];
     DMat<N> D;
     double grav;
@@ -905,6 +907,7 @@ template <int N, bool FULL>
 struct HalfOp {
     using C = HalfCf<N>;
     static constexpr int H = C::H, XT = N + H, S = XT + (FULL ? 1 : 0), NC = C::COUNT;
+    static constexpr bool NAN_ENDS = false;
     const double (*sc)[32];
     DMat<N> D;
     double gg;   // g in the lanes of rho', 0 in those of w

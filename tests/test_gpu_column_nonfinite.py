@@ -42,3 +42,24 @@ def test_nonfinite_column(N, nelz, restart, schur, field, level):
         assert not np.all(np.isfinite(y[:, :, 2]))
         np.testing.assert_array_equal(m[rest], n[rest])
         np.testing.assert_array_equal(y[:, :, rest], x[:, :, rest])
+
+
+# a reduced system with a NaN takes one step a cycle in every column of the wavefront,
+# so that such a column costs the solve no more than the others do
+@pytest.mark.parametrize("N,nelz", [(2, 1), (3, 5), (4, 16), (5, 10), (6, 2), (6, 10), (4, 17)])
+@pytest.mark.parametrize("restart,mr", [(10, 0), (10, 7)])
+def test_nan_ends_a_cycle(N, nelz, restart, mr):
+    import torch
+    from paper_2504_08157_amd import nhsem
+    mesh = W.MeshSpec((2, 1, nelz), N, W.uniform_edges(0, 20e3, 2), W.uniform_edges(0, 10e3, 1),
+                      W.uniform_edges(0, 15e3, nelz), (True, True))
+    ctx = nhsem.Context(mesh, W.Physics())
+    ctx.nh_set_reference(*W.constant_n_reference(ctx.nh_lattice_coords()[2]))
+    ncol = ctx.nx * ctx.ny
+    b = np.full((5, ctx.nz, ncol), 1e-2)
+    b[3, 1] = np.nan
+    it = torch.zeros(ncol, dtype=torch.int32, device="cuda")
+    x, st = ctx.nh_column_solve(0.4, torch.from_numpy(b.reshape(5, -1)).cuda(), restart=restart, max_restarts=mr,
+                                iters=it, schur=True, check=False)
+    assert st.not_converged == ncol
+    np.testing.assert_array_equal(it.cpu().numpy(), -(mr + 1) - 1)
